@@ -113,3 +113,38 @@ def test_sweep_on_oracle_cascade_outputs():
     want, best = check(score, conf, truth, deltas, W.PREV, wl.delta, 0.05, 0.05)
     print(dict(frames=n, positives=int(want[0]["positives"]), best=best,
                feasible=int(want["feasible"].sum())))
+
+
+@pytest.mark.parametrize("n,shift,shape", [
+    (4095, 0, "spread"), (4096, 0, "ones"), (4097, 1, "spread"),  # a step's edges, unaligned logs
+    (20_003, 0, "near"), (20_003, 3, "equal"),                    # one bin of every level; one value
+    (393_216, 0, "near"), (393_217, 0, "spread")])                # most frames kept in LDS, one more
+def test_sweep_counting_levels(n, shift, shape):
+    """Logs at the edges of the counting kernel: whole and ragged steps, log
+    arrays off their 16-byte alignment, confidences that share their upper
+    bits (so that every level decides), and logs too long for LDS."""
+    score, conf, truth = synthetic_log(n, 11)
+    r = np.random.default_rng(n)
+    if shape == "near":  # 1,000 neighbouring floats
+        conf = (np.uint32(0x3F7C1234) + r.integers(0, 1000, n).astype(np.uint32)).view(np.float32)
+    elif shape == "equal":
+        conf = np.full(n, 0.625, np.float32)
+    elif shape == "ones":
+        conf = r.choice(np.array([1.0, 0.0, 1e-45, 0.9999999], np.float32), n)
+    score[:15] = np.inf
+    deltas = np.array([-np.inf, 2.0, 8.0, 14.0, np.inf])
+    want, wbest = oracle.threshold_sweep(score, conf, truth, deltas, ref_mode=W.PREV, delta=15,
+                                         fp_target=0.03, fn_target=0.02, **COSTS)
+
+    def dev(v):  # `shift` elements past an aligned address
+        t = torch.zeros(len(v) + shift, dtype=torch.from_numpy(v[:1].copy()).dtype, device=DEV)
+        t[shift:] = torch.from_numpy(v).to(DEV)
+        return t[shift:]
+    rows = torch.zeros(len(deltas) * nsc.SWEEP_ROW_BYTES, dtype=torch.uint8, device=DEV)
+    best = torch.full((1,), -7, dtype=torch.int32, device=DEV)
+    cfg = nsc.SweepCfg(W.PREV, 15, 0.03, 0.02, COSTS["t_mse"], COSTS["t_snn"], COSTS["t_full"])
+    nsc.nsc_threshold_sweep(cfg, dev(score), dev(conf), dev(truth), dev(deltas), rows, best)
+    got = rows.cpu().numpy().view(oracle.SWEEP_ROW)
+    for k in range(len(deltas)):
+        assert all(got[k][f] == want[k][f] for f in FIELDS), (k, got[k], want[k])
+    assert int(best.item()) == wbest
