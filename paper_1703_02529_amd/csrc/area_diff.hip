@@ -77,9 +77,9 @@ template <int M>
 struct DiffSums {
   int64_t e = 0, s = 0, r = 0;
   __device__ __forceinline__ void add(int32_t x, int32_t y) {
-    const int64_t d = (int64_t)x - y;
-    if constexpr (M != NSC_METRIC_SAD) e += d * d;
-    if constexpr (M == NSC_METRIC_SAD) s += d < 0 ? -d : d;
+    const int32_t d = x - y;  // sums lie in [0, 2^31)
+    if constexpr (M != NSC_METRIC_SAD) e += (int64_t)d * d;
+    if constexpr (M == NSC_METRIC_SAD) s += (int64_t)(d < 0 ? -d : d);
     if constexpr (M == NSC_METRIC_NRMSE) r += (int64_t)y * y;
   }
   __device__ __forceinline__ void reduce() {
@@ -506,25 +506,43 @@ __global__ void __launch_bounds__(256) k_area_prev_wave(const uint8_t* __restric
 
 // ------------------------------------------------------------- detector
 
-// Blocked score by rows: a wave streams the frame row by row, lane l taking
-// values l + 64 j of each row (coalesced), whose block column is fixed; the
-// lane keeps one partial sum per slot j over a block row's rows, and at the
-// end of the block row the slots are added into per-block LDS sums (64-bit
-// LDS atomics, exact), from which lane bx computes block bx's metric.  Rows
-// of up to 64 x kDiffSlots values and up to 64 block columns.
+// A frame is scored by W waves of one workgroup: four, except for blocked
+// scores of many frames (W = 1: four frames per workgroup).  What bounds it:
+// the two reads of the sums, of which the second (frame t - delta) is near in
+// time when each XCD scores a contiguous range of frames (xcd_block) and then
+// hits its L2, and for few frames the length of one wave's chain of loads.
+// Four waves per frame on contiguous ranges, against one wave per frame and
+// frames dealt over the XCDs: 50x50 sums 4.0 us against 14.6 (30 frames), 6.8
+// against 14.1 (1,000), 37.6 against 69.0 (8,000), 546 against 795 (100,000);
+// blocked 10x10 on 100x100 sums 11.4 us against 44.3 (100 frames), 51.8 against
+// 67.6 (2,040), 392 against 417 (16,384, delta 1).  At 32,768 blocked frames
+// (delta 30) one wave per frame took 854 us, four 1,022 and the dealt order
+// 864: the sums no longer stay in the last-level cache between the two reads,
+// and fewer frames in flight keep more of them there.
+constexpr int64_t kDiffWideBlocked = 16384;
+
+// Blocked score by rows: a wave streams block rows (of its share) row by row,
+// lane l taking values l + 64 j of each row (coalesced), whose block column is
+// fixed; the lane keeps one partial sum per slot j over a block row's rows,
+// and at the end of the block row the slots are added into per-block LDS sums
+// (64-bit LDS atomics, exact), from which lane bx computes block bx's metric
+// times its weight.  Rows of up to 64 x kDiffSlots values and up to 64 block
+// columns.
 constexpr int kDiffSlots = 6;
 
 struct BlockRowSums {  // one wave's sums of the block row in progress
   unsigned long long e[64], s[64], r[64];
 };
 
-template <int M, int J>  // J = slots per lane: rows of 64 (J - 1) + 1 .. 64 J values
-__device__ __forceinline__ double blocked_score_rows(const int32_t* __restrict__ cur,
-                                                     const int32_t* __restrict__ ref,
-                                                     const DiffArgs& a, int32_t grid_h,
-                                                     int32_t grid_w, const float* lr_w,
-                                                     double lr_b, int lane, BlockRowSums* bs) {
+template <int M, int J, int W>  // J = slots per lane: rows of 64 (J - 1) + 1 .. 64 J values
+__device__ __forceinline__ double block_row_terms(const int32_t* __restrict__ cur,
+                                                const int32_t* __restrict__ ref,
+                                                const DiffArgs& a, int32_t grid_h,
+                                                int32_t grid_w, const float* lr_w, double lr_b,
+                                                int wave, int lane, BlockRowSums* bs,
+                                                double* terms) {
 #pragma clang fp contract(off)
+  double z = lr_b;
   const int rl = a.dd_w * 3;  // values per row
   // every lane loads all J slots (from value 0 where a slot is past the row,
   // counted as no difference) so that the loads of a row issue together
@@ -535,8 +553,7 @@ __device__ __forceinline__ double blocked_score_rows(const int32_t* __restrict__
     bxs[j] = c < rl ? ((c / 3 + 1) * grid_w - 1) / a.dd_w : -1;
     off[j] = c < rl ? c : 0;
   }
-  double z = lr_b;
-  for (int by = 0; by < grid_h; ++by) {
+  for (int by = wave; by < grid_h; by += W) {
     const int y0 = (int)((int64_t)by * a.dd_h / grid_h);
     const int y1 = (int)((int64_t)(by + 1) * a.dd_h / grid_h);
     DiffSums<M> acc[J];
@@ -568,7 +585,7 @@ __device__ __forceinline__ double blocked_score_rows(const int32_t* __restrict__
         atomicAdd(&bs->r[bxs[j]], (unsigned long long)acc[j].r);
     }
     __syncwarp();  // block sums complete
-    double m = 0.0;
+    double term = 0.0;
     if (lane < grid_w) {
       DiffSums<M> b;
       b.e = (int64_t)bs->e[lane];
@@ -577,23 +594,25 @@ __device__ __forceinline__ double blocked_score_rows(const int32_t* __restrict__
       const int x0 = (int)((int64_t)lane * a.dd_w / grid_w);
       const int x1 = (int)((int64_t)(lane + 1) * a.dd_w / grid_w);
       const double ncell = ((double)(y1 - y0) * (double)(x1 - x0)) * 3.0;
-      m = b.value(a, ncell);
+      term = (double)lr_w[by * grid_w + lane] * b.value(a, ncell);
+      if constexpr (W > 1) terms[by * grid_w + lane] = term;
     }
     __syncwarp();  // sums read before the next block row clears them
-    // in block order, as separate multiplies and adds
-    for (int bx = 0; bx < grid_w; ++bx) z = z + (double)lr_w[by * grid_w + bx] * __shfl(m, bx, 64);
+    if constexpr (W == 1)
+      for (int bx = 0; bx < grid_w; ++bx) z = z + __shfl(term, bx, 64);
   }
   return z;
 }
 
 // The detector score of one frame (area sums `cur`) against its reference
-// `ref`, by one wave: the metric over the whole grid, or the logistic score of
-// the per-block metrics (blocks in row-major order, weights lr_w).
-template <int M, bool BLK>  // BLK: blocked grids possible (else grid_h = grid_w = 1)
+// `ref`, by W waves: the metric over the whole grid, or the logistic score of
+// the per-block metrics (blocks in row-major order, weights lr_w).  Valid in
+// wave 0; every wave of the workgroup takes part when W > 1.
+template <int M, bool BLK, int W>  // BLK: blocked grids possible (else grid_h = grid_w = 1)
 __device__ __forceinline__ double frame_score(const int32_t* cur, const int32_t* ref,
                                               const DiffArgs& a, int32_t grid_h, int32_t grid_w,
-                                              const float* lr_w, double lr_b, int lane,
-                                              BlockRowSums* bs) {
+                                              const float* lr_w, double lr_b, int wave, int lane,
+                                              BlockRowSums* bs, double* terms, int64_t* red) {
   // the blocked score is summed with separate multiplies and adds, in block
   // order, so it is reproducible bit for bit
 #pragma clang fp contract(off)
@@ -603,25 +622,53 @@ __device__ __forceinline__ double frame_score(const int32_t* cur, const int32_t*
     if ((cells & 3) == 0 && (((uintptr_t)cur | (uintptr_t)ref) & 15) == 0) {
       const int4* c4 = reinterpret_cast<const int4*>(cur);
       const int4* r4 = reinterpret_cast<const int4*>(ref);
-      for (int64_t k = lane; k < cells / 4; k += 64) {
-        const int4 x = c4[k], y = r4[k];
-        acc.add(x.x, y.x);
-        acc.add(x.y, y.y);
-        acc.add(x.z, y.z);
-        acc.add(x.w, y.w);
+      // batches of U loads per lane and side in flight (past the end: no difference)
+      constexpr int U = 4;
+      const int64_t q = cells / 4;
+      for (int64_t k0 = lane + 64 * wave; k0 < q; k0 += (int64_t)64 * W * U) {
+        int4 x[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t k = k0 + (int64_t)64 * W * u;
+          x[u] = k < q ? c4[k] : make_int4(0, 0, 0, 0);
+          y[u] = k < q ? r4[k] : make_int4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          acc.add(x[u].x, y[u].x);
+          acc.add(x[u].y, y[u].y);
+          acc.add(x[u].z, y[u].z);
+          acc.add(x[u].w, y[u].w);
+        }
       }
     } else {
-      for (int64_t k = lane; k < cells; k += 64) acc.add(cur[k], ref[k]);
+      for (int64_t k = lane + 64 * wave; k < cells; k += 64 * W) acc.add(cur[k], ref[k]);
     }
     acc.reduce();
+    if constexpr (W > 1) {  // the other waves' exact sums
+      if (lane == 0) {
+        red[3 * wave] = acc.e;
+        red[3 * wave + 1] = acc.s;
+        red[3 * wave + 2] = acc.r;
+      }
+      __syncthreads();
+      acc = DiffSums<M>();
+      for (int w = 0; w < W; ++w) {
+        acc.e += red[3 * w];
+        acc.s += red[3 * w + 1];
+        acc.r += red[3 * w + 2];
+      }
+    }
     return acc.value(a, (double)cells);
   }
   if constexpr (!BLK) return 0.0;
+  double z = lr_b;
   if (grid_w <= 64 && a.dd_w * 3 <= 64 * kDiffSlots) {
     switch ((a.dd_w * 3 + 63) / 64) {
-#define NSC_ROWS_CASE(J) \
-  case J:                \
-    return blocked_score_rows<M, J>(cur, ref, a, grid_h, grid_w, lr_w, lr_b, lane, bs);
+#define NSC_ROWS_CASE(J)                                                                         \
+  case J:                                                                                        \
+    z = block_row_terms<M, J, W>(cur, ref, a, grid_h, grid_w, lr_w, lr_b, wave, lane, bs, terms); \
+    break;
       NSC_ROWS_CASE(1)
       NSC_ROWS_CASE(2)
       NSC_ROWS_CASE(3)
@@ -632,26 +679,36 @@ __device__ __forceinline__ double frame_score(const int32_t* cur, const int32_t*
       default:
         break;
     }
-  }
-  double z = lr_b;
-  for (int by = 0; by < grid_h; ++by) {
-    const int y0 = (int)((int64_t)by * a.dd_h / grid_h);
-    const int y1 = (int)((int64_t)(by + 1) * a.dd_h / grid_h);
-    for (int bx = 0; bx < grid_w; ++bx) {
+  } else {
+    for (int k = wave; k < grid_h * grid_w; k += W) {
+      const int by = k / grid_w, bx = k - by * grid_w;
+      const int y0 = (int)((int64_t)by * a.dd_h / grid_h);
+      const int y1 = (int)((int64_t)(by + 1) * a.dd_h / grid_h);
       const int x0 = (int)((int64_t)bx * a.dd_w / grid_w);
       const int x1 = (int)((int64_t)(bx + 1) * a.dd_w / grid_w);
       const int rl = (x1 - x0) * 3;
       const int total = (y1 - y0) * rl;
       DiffSums<M> acc;
-      for (int k = lane; k < total; k += 64) {
-        const int r = k / rl, cc = k - r * rl;
+      for (int e = lane; e < total; e += 64) {
+        const int r = e / rl, cc = e - r * rl;
         const int64_t off = ((int64_t)(y0 + r) * a.dd_w + x0) * 3 + cc;
         acc.add(cur[off], ref[off]);
       }
       acc.reduce();
       const double ncell = ((double)(y1 - y0) * (double)(x1 - x0)) * 3.0;
-      const double m = acc.value(a, ncell);
-      z = z + (double)lr_w[by * grid_w + bx] * m;
+      const double term = (double)lr_w[k] * acc.value(a, ncell);
+      if constexpr (W == 1)
+        z = z + term;
+      else if (lane == 0)
+        terms[k] = term;
+    }
+  }
+  if constexpr (W > 1) {  // in block order, as separate multiplies and adds
+    __syncthreads();
+    const int nb = grid_h * grid_w;
+    if (wave == 0) {
+#pragma unroll 8
+      for (int k = 0; k < nb; ++k) z = z + terms[k];
     }
   }
   return z;
@@ -671,33 +728,48 @@ __device__ __forceinline__ double part_score(const DiffArgs& a, int64_t i, int l
   return acc.value(a, (double)((int64_t)a.dd_h * a.dd_w * 3));
 }
 
-// The fixed-reference detector fused into the area kernel: a thread per
-// frame adds the frame's per-unit partial sums (exact integers, so their order
-// does not matter) and applies the metric as k_diff does.
+// The fixed-reference detector fused into the area kernel: a wave per frame
+// adds the frame's per-unit partial sums (exact integers, so their order
+// does not matter) and applies the metric as k_diff does.  (1,024 frames of
+// 720p, 100 units each: 5 us, against 26.8 for a thread per frame, whose loads
+// followed one another 24 bytes at a time.)
 template <int M>
 __global__ void __launch_bounds__(256) k_diff_fixed_finish(DiffArgs a, const int64_t* __restrict__ part,
                                                            int32_t units) {
 #pragma clang fp contract(off)
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= a.n) return;
   DiffSums<M> acc;
   const int64_t* p = part + i * units * 3;
-  for (int u = 0; u < units; ++u) {
+  for (int u = lane; u < units; u += 64) {
     acc.e += p[3 * u];
     acc.s += p[3 * u + 1];
     acc.r += p[3 * u + 2];
   }
+  acc.reduce();
   const double score = acc.value(a, (double)((int64_t)a.dd_h * a.dd_w * 3));
-  a.fire[i] = score > a.delta_diff ? 1 : 0;
-  if (a.score) a.score[i] = score;
+  if (lane == 0) {
+    a.fire[i] = score > a.delta_diff ? 1 : 0;
+    if (a.score) a.score[i] = score;
+  }
 }
 
-template <int M, bool BLK>
+// LDS of the scoring kernels.
+template <bool BLK, int W>
+struct DiffShared {
+  BlockRowSums bsums[BLK ? 4 : 1];
+  double terms[BLK && W > 1 ? NSC_MAX_BLOCKS : 1];  // weight times metric, in block order
+  int64_t red[3 * W];
+};
+
+template <int M, bool BLK, int W>
 __global__ void __launch_bounds__(256) k_diff(DiffArgs a) {
-  __shared__ BlockRowSums bsums[4];
+  __shared__ DiffShared<BLK, W> sh;
   const int lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= a.n) return;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = xcd_block(blockIdx.x, gridDim.x) * (4 / W) + wv / W;
+  if (i >= a.n) return;  // the whole workgroup when W = 4
   const int64_t t = a.t0 + i;
   const int64_t cells = (int64_t)a.dd_h * a.dd_w * 3;
   const bool forced = a.ref_mode == NSC_REF_PREV && t < a.delta;
@@ -705,7 +777,7 @@ __global__ void __launch_bounds__(256) k_diff(DiffArgs a) {
   const bool from_part = M == NSC_METRIC_MSE && !BLK && a.part != nullptr && !forced &&
                          (i / a.delta) % a.chain_r != 0;
   if (from_part) {
-    score = part_score(a, i, lane);
+    if (wv % W == 0) score = part_score(a, i, lane);
   } else if (!forced) {
     const int32_t* cur = a.sums + i * cells;
     const int32_t* ref;
@@ -715,10 +787,10 @@ __global__ void __launch_bounds__(256) k_diff(DiffArgs a) {
       ref = a.sums + (i - a.delta) * cells;
     else
       ref = a.prev_sums + i * cells;  // frame t - delta = t0 - delta + i
-    score = frame_score<M, BLK>(cur, ref, a, a.grid_h, a.grid_w, a.lr_w, a.lr_b, lane,
-                          &bsums[threadIdx.x >> 6]);
+    score = frame_score<M, BLK, W>(cur, ref, a, a.grid_h, a.grid_w, a.lr_w, a.lr_b, wv % W, lane,
+                                   &sh.bsums[BLK ? wv : 0], sh.terms, sh.red);
   }
-  if (lane == 0) {
+  if (lane == 0 && wv % W == 0) {
     a.fire[i] = (forced || score > a.delta_diff) ? 1 : 0;
     if (a.score) a.score[i] = score;
   }
@@ -728,12 +800,13 @@ __global__ void __launch_bounds__(256) k_diff(DiffArgs a) {
 // frames c * n .. c * n + n - 1 of the batch, each scored with its camera's
 // reference, blocks, weights and threshold; the frames before t0 come from
 // the camera's state slot.
-template <int M, bool BLK>
+template <int M, bool BLK, int W>
 __global__ void __launch_bounds__(256) k_diff_group(DiffArgs a) {
-  __shared__ BlockRowSums bsums[4];
+  __shared__ DiffShared<BLK, W> sh;
   const int lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= a.n) return;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = xcd_block(blockIdx.x, gridDim.x) * (4 / W) + wv / W;
+  if (i >= a.n) return;  // the whole workgroup when W = 4
   const int64_t cam = i / a.per_cam;
   const int64_t j = i - cam * a.per_cam;
   const CamDiff cd = a.cams[cam];
@@ -750,10 +823,10 @@ __global__ void __launch_bounds__(256) k_diff_group(DiffArgs a) {
       ref = a.sums + (i - cd.delta) * cells;
     else  // frame t0 - delta + j, kept in the camera's state
       ref = reinterpret_cast<const int32_t*>(a.state + cam * a.state_stride) + j * cells;
-    score = frame_score<M, BLK>(cur, ref, a, cd.grid_h, cd.grid_w, cd.lr_w, cd.lr_b, lane,
-                          &bsums[threadIdx.x >> 6]);
+    score = frame_score<M, BLK, W>(cur, ref, a, cd.grid_h, cd.grid_w, cd.lr_w, cd.lr_b, wv % W,
+                                   lane, &sh.bsums[BLK ? wv : 0], sh.terms, sh.red);
   }
-  if (lane == 0) {
+  if (lane == 0 && wv % W == 0) {
     a.fire[i] = (forced || score > cd.delta_diff) ? 1 : 0;
     if (a.score) a.score[i] = score;
   }
@@ -901,17 +974,23 @@ int launch_area_sums(const AreaPlan& p, const uint8_t* frames, int64_t stride, i
 
 int launch_diff(const DiffArgs& a, hipStream_t stream) {
   if (a.n <= 0) return NSC_OK;
-  const int64_t blocks = (a.n + 3) / 4;
+  const bool blocked = a.cams ? a.cams_blocked != 0 : a.grid_h * a.grid_w > 1;
+  const bool wide = !blocked || a.n < kDiffWideBlocked;  // four waves per frame
+  const int64_t blocks = wide ? a.n : (a.n + 3) / 4;
   if (blocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
-#define NSC_DIFF_LAUNCH(M)                                                                    \
-  if (a.cams && a.cams_blocked)                                                               \
-    hipLaunchKernelGGL((k_diff_group<M, true>), dim3((unsigned)blocks), dim3(256), 0, stream, a); \
-  else if (a.cams)                                                                            \
-    hipLaunchKernelGGL((k_diff_group<M, false>), dim3((unsigned)blocks), dim3(256), 0, stream, a); \
-  else if (a.grid_h * a.grid_w > 1)                                                           \
-    hipLaunchKernelGGL((k_diff<M, true>), dim3((unsigned)blocks), dim3(256), 0, stream, a);   \
+#define NSC_DIFF_LAUNCH2(K, M)                                                                \
+  if (!blocked)                                                                               \
+    hipLaunchKernelGGL((K<M, false, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);    \
+  else if (wide)                                                                              \
+    hipLaunchKernelGGL((K<M, true, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);     \
   else                                                                                        \
-    hipLaunchKernelGGL((k_diff<M, false>), dim3((unsigned)blocks), dim3(256), 0, stream, a)
+    hipLaunchKernelGGL((K<M, true, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a)
+#define NSC_DIFF_LAUNCH(M)                                                                    \
+  if (a.cams) {                                                                               \
+    NSC_DIFF_LAUNCH2(k_diff_group, M);                                                        \
+  } else {                                                                                    \
+    NSC_DIFF_LAUNCH2(k_diff, M);                                                              \
+  }
   switch (a.metric) {
     case NSC_METRIC_MSE:
       NSC_DIFF_LAUNCH(NSC_METRIC_MSE);
@@ -929,6 +1008,7 @@ int launch_diff(const DiffArgs& a, hipStream_t stream) {
       return fail(NSC_E_INVAL, "metric %d is unknown", a.metric);
   }
 #undef NSC_DIFF_LAUNCH
+#undef NSC_DIFF_LAUNCH2
   NSC_CHECK_LAUNCH("k_diff");
   return NSC_OK;
 }
@@ -1029,7 +1109,7 @@ int launch_area_detect_fixed(const AreaPlan& p, const uint8_t* frames, int64_t s
     if (p.packed) NSC_FUSED_LAUNCH(4, true, M); else NSC_FUSED_LAUNCH(4, false, M);              \
   }                                                                                              \
   NSC_CHECK_LAUNCH("k_area_sums_wave (fused detector)");                                         \
-  hipLaunchKernelGGL((k_diff_fixed_finish<M>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,  \
+  hipLaunchKernelGGL((k_diff_fixed_finish<M>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0,      \
                      stream, a, (const int64_t*)part, (int32_t)(g.bands * g.waves_per_frame));   \
   NSC_CHECK_LAUNCH("k_diff_fixed_finish")
   switch (a.metric) {

@@ -558,3 +558,38 @@ def test_skipping_streamed_equals_one_shot():
     for k in keys:
         assert np.array_equal(np.nan_to_num(g[k], nan=-7), np.nan_to_num(ref[k], nan=-7)), k
     print(check_samples(wl, v, blob, lr, None, g, [0, 1, 2, 301, 302, 603, 1299]))
+
+
+@pytest.mark.parametrize("H,W,grid", [
+    (12, 10, (3, 5)),      # rows of blocks, one slot per lane
+    (20, 130, (7, 13)),    # rows of 390 values: the general block walk
+    (8, 72, (2, 70)),      # more block columns than lanes
+    (6, 8, (1, 1)),
+])
+def test_detector_frame_splits(H, W, grid):
+    """A call scored by one wave per frame (blocked, from 16,384 frames on) or
+    four gives the scores of the same frames in small calls, bit for bit, and
+    the oracle's at sampled frames."""
+    n, delta = 16_400, 3
+    frames = torch.from_numpy(rng.integers(0, 256, size=(n, H, W, 3), dtype=np.uint8)).to(DEV)
+    lr = rng.standard_normal(grid[0] * grid[1]).astype(np.float32)
+    lr_dev = _dev(lr)
+    cfg = nsc.make_cfg(in_h=H, in_w=W, dd_h=H, dd_w=W, cnn_h=H, cnn_w=W, delta=delta, grid=grid,
+                       lr_w=lr_dev if grid != (1, 1) else None, lr_b=0.25, delta_diff=0.0)
+    sums = torch.empty((n, H, W, 3), dtype=torch.int32, device=DEV)
+    fire = torch.empty(n, dtype=torch.uint8, device=DEV)
+    score = torch.empty(n, dtype=torch.float64, device=DEV)
+    nsc.nsc_diff_detect(cfg, frames, n, 0, sums, fire, score_out=score)
+    a, b = 16_000, 16_300
+    part = torch.empty(b - a, dtype=torch.float64, device=DEV)
+    pfire = torch.empty(b - a, dtype=torch.uint8, device=DEV)
+    psums = torch.empty((b - a, H, W, 3), dtype=torch.int32, device=DEV)
+    nsc.nsc_diff_detect(cfg, frames[a:b], b - a, a, psums, pfire, score_out=part,
+                        prev_sums=sums[a - delta:a])
+    assert torch.equal(part, score[a:b]) and torch.equal(pfire, fire[a:b])
+    S, g = sums.cpu().numpy(), score.cpu().numpy()
+    assert np.isinf(g[:delta]).all()
+    for i in (3, 77, 9_999, n - 1):
+        exp = (oracle.global_mse(S[i], S[i - delta], 1)[0] if grid == (1, 1) else
+               oracle.blocked_score(S[i], S[i - delta], 1, grid, lr, 0.25)[0])
+        assert g[i] == exp, (i, g[i], exp)
