@@ -849,12 +849,11 @@ int run_checked(const nsc_cascade_cfg* cfg, const Cnn& c, const uint8_t* frames,
   }
   if (int rc = mark(2)) return rc;
   // 3: compaction
-  if (int rc = launch_compact(fire, n, idx, count, reinterpret_cast<int32_t*>(w + L.tiles), st))
+  if (int rc = launch_compact(fire, n, idx, count, reinterpret_cast<int32_t*>(w + L.tiles), st,
+                              logit_out))
     return rc;
   if (int rc = mark(3)) return rc;
   // 4: CNN on survivors with decisions written at their frame positions
-  if (logit_out)
-    if (int rc = launch_fill_nan(logit_out, n, st)) return rc;
   CnnRunArgs r{};
   r.sums = sums;
   r.sums_h = cfg->dd_h;
@@ -885,17 +884,12 @@ int run_checked(const nsc_cascade_cfg* cfg, const Cnn& c, const uint8_t* frames,
     if (int rc = run_cnn(c, r, w + L.cnn, L.total - L.cnn, st)) return rc;
   }
   if (int rc = mark(4)) return rc;
-  // 5: decisions of frames that did not fire
+  // 5: decisions of frames that did not fire, and the state after the call
   const ResolvePlan rp = make_resolve_plan(n, t0, prev ? cfg->delta : 1);
-  if (int rc = launch_resolve(rp, cfg->ref_mode, fire, dec, st_dec,
-                              reinterpret_cast<int32_t*>(w + L.tile_last),
-                              reinterpret_cast<int32_t*>(w + L.carry), label_out, defer_out, st))
-    return rc;
-  if (prev)
-    if (int rc = launch_state_update(sums, label_out, defer_out, n, cfg->delta, cells, st_sums,
-                                     st_dec, w + L.scratch, st))
-      return rc;
-  return NSC_OK;
+  const StreamState ss{st_sums, st_dec, w + L.scratch};
+  return launch_resolve(rp, cfg->ref_mode, fire, dec, reinterpret_cast<int32_t*>(w + L.tile_last),
+                        reinterpret_cast<int32_t*>(w + L.carry), label_out, defer_out, sums, cells,
+                        ss, st);
 }
 
 }  // namespace
@@ -1351,12 +1345,11 @@ int nsc_group_run(const nsc_group* g, const uint8_t* frames, int64_t n, int64_t 
   }
   if (int rc = mark(2)) return rc;
   // 3: compaction over all cameras (survivors in camera-major frame order)
-  if (int rc = launch_compact(fire, N, idx, count, reinterpret_cast<int32_t*>(w + L.tiles), st))
+  if (int rc = launch_compact(fire, N, idx, count, reinterpret_cast<int32_t*>(w + L.tiles), st,
+                              outs ? outs->logit : nullptr))
     return rc;
   if (int rc = mark(3)) return rc;
   // 4: CNN, every survivor with its camera's network and thresholds
-  if (outs && outs->logit)
-    if (int rc = launch_fill_nan(outs->logit, N, st)) return rc;
   CnnRunArgs r{};
   r.sums = sums;
   r.sums_h = cfg->dd_h;
@@ -1377,13 +1370,9 @@ int nsc_group_run(const nsc_group* g, const uint8_t* frames, int64_t n, int64_t 
   if (int rc = run_cnn(c, r, w + L.cnn, L.total - L.cnn, st)) return rc;
   if (int rc = mark(4)) return rc;
   // 5: decisions of the frames that did not fire, then the cameras' state
-  if (int rc = launch_group_resolve(g->cams, g->n_cams, fire, dec, n, t0, st_bytes, g->slot,
-                                    label_out, defer_out, st))
+  if (int rc = launch_group_resolve(g->cams, g->n_cams, g->max_delta, fire, dec, sums, cells, n, t0,
+                                    st_bytes, g->slot, w + L.scratch, label_out, defer_out, st))
     return rc;
-  if (g->max_delta > 0)
-    if (int rc = launch_group_state(g->cams, g->n_cams, g->max_delta, sums, label_out, defer_out,
-                                    n, cells, st_bytes, g->slot, w + L.scratch, st))
-      return rc;
   if (int rc = mark(5)) return rc;
   if (stats) {
     std::vector<uint8_t> hl(N), hdf(N);

@@ -507,7 +507,8 @@ __global__ void __launch_bounds__(256) k_area_prev_wave(const uint8_t* __restric
 // ------------------------------------------------------------- detector
 
 // A frame is scored by W waves of one workgroup: four, except for blocked
-// scores of many frames (W = 1: four frames per workgroup).  What bounds it:
+// scores of many frames and for grids of a few hundred values (W = 1: four
+// frames per workgroup).  What bounds it:
 // the two reads of the sums, of which the second (frame t - delta) is near in
 // time when each XCD scores a contiguous range of frames (xcd_block) and then
 // hits its L2, and for few frames the length of one wave's chain of loads.
@@ -975,16 +976,20 @@ int launch_area_sums(const AreaPlan& p, const uint8_t* frames, int64_t stride, i
 int launch_diff(const DiffArgs& a, hipStream_t stream) {
   if (a.n <= 0) return NSC_OK;
   const bool blocked = a.cams ? a.cams_blocked != 0 : a.grid_h * a.grid_w > 1;
-  const bool wide = !blocked || a.n < kDiffWideBlocked;  // four waves per frame
+  // four waves per frame; one where a frame is no more than a load or two of a wave
+  // (65,536 frames of 8x8 sums: 20 us against 60)
+  const bool wide = (int64_t)a.dd_h * a.dd_w * 3 > 1024 && (!blocked || a.n < kDiffWideBlocked);
   const int64_t blocks = wide ? a.n : (a.n + 3) / 4;
   if (blocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
 #define NSC_DIFF_LAUNCH2(K, M)                                                                \
-  if (!blocked)                                                                               \
-    hipLaunchKernelGGL((K<M, false, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);    \
-  else if (wide)                                                                              \
+  if (blocked && wide)                                                                        \
     hipLaunchKernelGGL((K<M, true, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);     \
+  else if (blocked)                                                                           \
+    hipLaunchKernelGGL((K<M, true, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a);     \
+  else if (wide)                                                                              \
+    hipLaunchKernelGGL((K<M, false, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, a);    \
   else                                                                                        \
-    hipLaunchKernelGGL((K<M, true, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a)
+    hipLaunchKernelGGL((K<M, false, 1>), dim3((unsigned)blocks), dim3(256), 0, stream, a)
 #define NSC_DIFF_LAUNCH(M)                                                                    \
   if (a.cams) {                                                                               \
     NSC_DIFF_LAUNCH2(k_diff_group, M);                                                        \

@@ -152,8 +152,9 @@ int launch_area_detect_fixed(const AreaPlan& p, const uint8_t* frames, int64_t s
 
 // Compaction of fire flags into ascending indices.
 int64_t compact_tiles(int64_t n);
+// nan_out (nullable): n floats set to NaN on the way.
 int launch_compact(const uint8_t* fire, int64_t n, int32_t* idx, int32_t* count, int32_t* tile_counts,
-                   hipStream_t stream);
+                   hipStream_t stream, float* nan_out = nullptr);
 // The same with the tile offsets in a static device array (no workspace).
 int launch_compact_noalloc(const uint8_t* fire, int64_t n, int32_t* idx, int32_t* count,
                            hipStream_t stream);
@@ -164,24 +165,27 @@ struct ResolvePlan {
   int32_t delta, rows_per_tile, tiles;
 };
 ResolvePlan make_resolve_plan(int64_t n, int64_t t0, int32_t delta);
+// What a stream carries from call to call (earlier-frame mode; null
+// otherwise): the area sums and decisions of its last delta frames, and
+// scratch of delta * (4 * cells + 1) bytes for calls shorter than delta.
+struct StreamState {
+  int32_t* sums;
+  uint8_t* dec;
+  void* scratch;
+};
+// Labels of a call's frames from the decisions of the fired ones, and the
+// state after the call.
 int launch_resolve(const ResolvePlan& p, int32_t ref_mode, const uint8_t* fire, const uint8_t* dec,
-                   const uint8_t* prev_dec, int32_t* tile_last, int32_t* carry, uint8_t* label,
-                   uint8_t* defer, hipStream_t stream);
-int launch_state_update(const int32_t* sums, const uint8_t* label, const uint8_t* defer, int64_t n,
-                        int32_t delta, int64_t cells, int32_t* state_sums, uint8_t* state_dec,
-                        void* scratch, hipStream_t stream);
-int launch_fill_nan(float* p, int64_t n, hipStream_t stream);
+                   int32_t* tile_last, int32_t* carry, uint8_t* label, uint8_t* defer,
+                   const int32_t* sums, int64_t cells, const StreamState& st, hipStream_t stream);
 // Camera groups: label resolution of n frames per camera, and the state slots
 // (the last delta frames of every earlier-frame camera; scratch holds a copy
 // of n_cams * state_stride bytes when n < max_delta).
-int launch_group_resolve(const CamDiff* cams, int32_t n_cams, const uint8_t* fire,
-                         const uint8_t* dec, int64_t n, int64_t t0, const unsigned char* state,
-                         int64_t state_stride, uint8_t* label, uint8_t* defer,
+int launch_group_resolve(const CamDiff* cams, int32_t n_cams, int32_t max_delta,
+                         const uint8_t* fire, const uint8_t* dec, const int32_t* sums,
+                         int64_t cells, int64_t n, int64_t t0, unsigned char* state,
+                         int64_t state_stride, void* scratch, uint8_t* label, uint8_t* defer,
                          hipStream_t stream);
-int launch_group_state(const CamDiff* cams, int32_t n_cams, int32_t max_delta,
-                       const int32_t* sums, const uint8_t* label, const uint8_t* defer, int64_t n,
-                       int64_t cells, unsigned char* state, int64_t state_stride, void* scratch,
-                       hipStream_t stream);
 int launch_set_i32(int32_t* p, int32_t v, hipStream_t stream);
 // *out = clamp(*count - off, 0, m): the survivors of the CNN pass over the
 // compacted slots [off, off + m).
