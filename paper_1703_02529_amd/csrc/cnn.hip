@@ -38,6 +38,7 @@
 // c_high decision of each frame.
 #include "nsc_internal.h"
 
+#include <limits.h>
 #include <math.h>
 
 namespace nsc {
@@ -263,7 +264,7 @@ struct ConvArgs {
 // (moved to scalar registers).
 __device__ __forceinline__ int64_t slot_woff(const CamNet* nets, int64_t per_cam,
                                              const int32_t* idx, int64_t s) {
-  const uint64_t off = (uint64_t)nets[idx[s] / per_cam].woff;
+  const uint64_t off = (uint64_t)nets[(uint32_t)idx[s] / (uint32_t)per_cam].woff;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)off);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(off >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
@@ -281,12 +282,28 @@ __device__ __forceinline__ void tile_pixel(int m, int& py, int& px) {
   px = 2 * (wi & 1) + (j & 1);
 }
 
+// The layer's packed weights into LDS rows of w_lds elements, 16 bytes at a
+// time (kpad and w_lds are whole 16-byte units), eight loads in flight per
+// thread: a workgroup of a small call waits for nothing else at its start.
 template <typename T>
 __device__ __forceinline__ void stage_weights(const ConvArgs& a, T* wl, int64_t off = 0) {
-  const T* src = at_off(reinterpret_cast<const T*>(a.wts), off);
-  for (int e = threadIdx.x; e < a.cout * a.kpad; e += blockDim.x) {
-    const int o = e / a.kpad, k = e - o * a.kpad;
-    wl[o * a.w_lds + k] = src[e];
+  constexpr int V = 16 / sizeof(T), B = 8;
+  const uint4* src = reinterpret_cast<const uint4*>(at_off(reinterpret_cast<const T*>(a.wts), off));
+  const int per = a.kpad / V, units = a.cout * per;
+  for (int u0 = threadIdx.x; u0 < units; u0 += B * blockDim.x) {
+    uint4 v[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int u = u0 + j * blockDim.x;
+      if (u < units) v[j] = src[u];
+    }
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int u = u0 + j * blockDim.x;
+      if (u >= units) break;
+      const int o = u / per;
+      *reinterpret_cast<uint4*>(wl + o * a.w_lds + (u - o * per) * V) = v[j];
+    }
   }
 }
 
@@ -791,7 +808,9 @@ __global__ void __launch_bounds__(1024) k_conv_pair(ConvArgs a0, ConvArgs a1, Pa
   }
   int64_t staged = 0;
   bool have = !G;
-  for (int i = threadIdx.x; i < 2 * a1.lo_plane; i += blockDim.x) in1[i] = 0;
+  // (lo_plane and in1's offset are multiples of 8 elements)
+  for (int i = threadIdx.x; i < 2 * a1.lo_plane / 8; i += blockDim.x)
+    reinterpret_cast<uint4*>(in1)[i] = make_uint4(0u, 0u, 0u, 0u);
   int64_t cnt = *a0.count;
   if (cnt > a0.max_count) cnt = a0.max_count;
   const int ho0 = a0.h / 2, wo0 = a0.w / 2;  // the first layer pools
@@ -1675,16 +1694,30 @@ struct DenseArgs {
   int64_t per_cam;
 };
 
+// Camera of survivor slot u of a camera group (slots are in frame order, so
+// the cameras of consecutive slots do not decrease).
+__device__ __forceinline__ int cam_at(const DenseArgs& a, int64_t u) {
+  return (int)((uint32_t)a.idx[u] / (uint32_t)a.per_cam);
+}
+// The smallest camera after cam among the wave's lanes' cameras (INT_MAX: none).
+__device__ __forceinline__ int next_cam(int mine, int cam) {
+  int v = mine > cam ? mine : INT_MAX;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) v = min(v, __shfl_xor(v, o, 64));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 // The output of one 16-survivor tile from its hidden pre-activations t (lane
 // (m, g): rows row0 + 4 g + r, units 16 nt + m): hidden = ReLU(t + b1),
-// z = b2 + sum_n w2[n] hidden[n] (a 16-lane shuffle reduction), then the
-// logit, the sigmoid and the decision at the frame's position, for the rows
-// of camera cam (every row without a camera group).
+// z = b2 + sum_n w2[n] hidden[n] (a 16-lane shuffle reduction), then, lane m of
+// 0..3 taking row 4 g + m, the logit, the sigmoid and the decision at the
+// frame's position, for the rows of camera cam (every row without a camera
+// group).
 template <int NT, bool G>
 __device__ __forceinline__ void dense_out(const DenseArgs& a, const f32x4 (&t)[NT],
                                           const float* b1, const float* w2, float b2,
                                           double c_low, double c_high, int64_t row0,
-                                          int64_t cnt, int64_t cam, int m, int g) {
+                                          int64_t cnt, int cam, int m, int g) {
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -1698,21 +1731,16 @@ __device__ __forceinline__ void dense_out(const DenseArgs& a, const f32x4 (&t)[N
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) sum[r] += __shfl_xor(sum[r], o, 64);
   }
-  if (m == 0) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t slot = row0 + 4 * g + r;
-      if (slot < cnt && (!G || a.idx[slot] / a.per_cam == cam)) {
-        const float z = sum[r] + b2;
-        const double p = 1.0 / (1.0 + exp(-(double)z));
-        a.logit[slot] = z;
-        if (a.prob) a.prob[slot] = (float)p;
-        if (a.dec || a.frame_logit) {
-          const int32_t f = a.idx[slot];
-          if (a.dec) a.dec[f] = p < c_low ? 0 : (p > c_high ? 1 : 2);
-          if (a.frame_logit) a.frame_logit[f] = z;
-        }
-      }
+  const int64_t slot = row0 + 4 * g + m;
+  if (m < 4 && slot < cnt && (!G || cam_at(a, slot) == cam)) {
+    const float z = (m == 0 ? sum[0] : m == 1 ? sum[1] : m == 2 ? sum[2] : sum[3]) + b2;
+    const double p = 1.0 / (1.0 + exp(-(double)z));
+    a.logit[slot] = z;
+    if (a.prob) a.prob[slot] = (float)p;
+    if (a.dec || a.frame_logit) {
+      const int32_t f = a.idx[slot];
+      if (a.dec) a.dec[f] = p < c_low ? 0 : (p > c_high ? 1 : 2);
+      if (a.frame_logit) a.frame_logit[f] = z;
     }
   }
 }
@@ -1746,13 +1774,12 @@ __global__ void __launch_bounds__(64 * kDenseWaves) k_dense(DenseArgs a) {
   const int64_t groups = (cnt + R - 1) / R;
   const int nks = (a.flat + KS - 1) / KS;  // K steps
   const int ks0 = wave * nks / NW, ks1 = (wave + 1) * nks / NW;
-  // camera of survivor slot u of a camera group (slots are in frame order, so
-  // a group's cameras are non-decreasing)
-  auto cam_of = [&](int64_t u) -> int64_t { return a.idx[u] / a.per_cam; };
   for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
     // A group runs once per camera among its rows (once without a camera
     // group), each pass with that camera's weights over its own rows.
-    int64_t cam = G ? cam_of(grp * R) : 0;
+    static_assert(R <= 64, "a lane per row");
+    const int mine = G && grp * R + lane % R < cnt ? cam_at(a, grp * R + lane % R) : INT_MAX;
+    int cam = G ? next_cam(mine, -1) : 0;
     for (;;) {
       int64_t off = 0;
       float b2 = a.b2;
@@ -1778,7 +1805,7 @@ __global__ void __launch_bounds__(64 * kDenseWaves) k_dense(DenseArgs a) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         const int64_t s = grp * R + mt * 16 + m;
-        valid[mt] = s < cnt && (!G || cam_of(s) == cam);
+        valid[mt] = s < cnt && (!G || cam_at(a, s) == cam);
         arow[mt] = a.feat + (valid[mt] ? s : 0) * (int64_t)a.flat + g * E;
       }
       f32x4 acc[MT][NT];
@@ -1836,14 +1863,8 @@ __global__ void __launch_bounds__(64 * kDenseWaves) k_dense(DenseArgs a) {
       }
       __syncthreads();  // the partial sums are read before the next pass writes them
       if constexpr (!G) break;
-      // the next camera among the group's rows (uniform)
-      int64_t next = -1;
-      for (int r = 0; r < R && next < 0; ++r) {
-        const int64_t u = grp * R + r;
-        if (u < cnt && cam_of(u) > cam) next = cam_of(u);
-      }
-      if (next < 0) break;
-      cam = next;
+      cam = next_cam(mine, cam);  // uniform
+      if (cam == INT_MAX) break;
     }
   }
 }
@@ -1885,7 +1906,6 @@ __global__ void __launch_bounds__(64 * kDenseSplitWaves) k_dense_part(DenseArgs 
   const int nks = (a.flat + KS - 1) / KS;
   const int kparts = dense_kparts(tiles, nks);
   const int64_t items = tiles * kparts;
-  auto cam_of = [&](int64_t u) -> int64_t { return a.idx[u] / a.per_cam; };
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t tile = item / kparts;
     const int kp = (int)(item - tile * kparts);
@@ -1895,12 +1915,13 @@ __global__ void __launch_bounds__(64 * kDenseSplitWaves) k_dense_part(DenseArgs 
     f32x4 acc[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int64_t cam = G ? cam_of(tile * 16) : 0;
+    const int mine = G && s < cnt ? cam_at(a, s) : INT_MAX;
+    int cam = G ? next_cam(mine, -1) : 0;
     for (;;) {
       const int64_t off = G ? (int64_t)a.nets[cam].woff : 0;
       const T* w1 = at_off(reinterpret_cast<const T*>(a.w1), off);
       const float in_scale = X::CVT ? at_off(a.scl, off)[0] : 1.0f;
-      const bool valid = s < cnt && (!G || cam_of(s) == cam);
+      const bool valid = s < cnt && (!G || mine == cam);
       const float* arow = a.feat + (valid ? s : 0) * (int64_t)a.flat + g * E;
       // as in k_dense: a lane group's E values of the last K step are all
       // inside or all past the end; hi and lo products share the accumulators
@@ -1910,8 +1931,12 @@ __global__ void __launch_bounds__(64 * kDenseSplitWaves) k_dense_part(DenseArgs 
         typename X::frag bv[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-          bv[nt] = X::zero();
-          if (kin) bv[nt] = X::load(w1 + (int64_t)(nt * 16 + m) * a.flat + k0 + g * E);
+          if constexpr (X::CVT) {  // fragment order, zero past the end
+            bv[nt] = reinterpret_cast<const typename X::frag*>(w1)[(ks * NT + nt) * 64 + lane];
+          } else {
+            bv[nt] = X::zero();
+            if (kin) bv[nt] = X::load(w1 + (int64_t)(nt * 16 + m) * a.flat + k0 + g * E);
+          }
         }
         typename X::frag av = X::zero(), av_lo = X::zero();
         if constexpr (SPLIT) {
@@ -1930,14 +1955,8 @@ __global__ void __launch_bounds__(64 * kDenseSplitWaves) k_dense_part(DenseArgs 
         }
       }
       if constexpr (!G) break;
-      // the next camera among the tile's rows (uniform)
-      int64_t next = -1;
-      for (int r = 0; r < 16 && next < 0; ++r) {
-        const int64_t u = tile * 16 + r;
-        if (u < cnt && cam_of(u) > cam) next = cam_of(u);
-      }
-      if (next < 0) break;
-      cam = next;
+      cam = next_cam(mine, cam);  // uniform
+      if (cam == INT_MAX) break;
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = acc[nt];
@@ -1985,7 +2004,6 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
   const int kparts = dense_tile_kparts(cnt, nks);
   const int64_t blocks = (cnt + kDenseTileRows - 1) / kDenseTileRows;
   const int64_t items = blocks * kparts;
-  auto cam_of = [&](int64_t u) -> int64_t { return a.idx[u] / a.per_cam; };
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t blk = item / kparts;
     const int kp = (int)(item - blk * kparts);
@@ -1999,7 +2017,7 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
     // In a camera group the block runs once per camera among its rows, each
     // pass with that camera's weights over its own rows (the other rows add
     // zero products, which leave their sums unchanged).
-    int64_t cam = G ? cam_of(blk * kDenseTileRows) : 0;
+    int cam = G ? cam_at(a, blk * kDenseTileRows) : 0;
     for (;;) {
       const int64_t off = G ? (int64_t)a.nets[cam].woff : 0;
       const float in_scale = at_off(a.scl, off)[0];
@@ -2009,7 +2027,7 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         const int64_t s = (tile0 + i) * 16 + m;
-        valid[i] = s < cnt && (!G || cam_of(s) == cam);
+        valid[i] = s < cnt && (!G || cam_at(a, s) == cam);
         row[i] = (valid[i] ? s : 0) * (int64_t)a.flat + g * 8;
       }
       // the activation fragment of K step ks for tile i (zero past the end)
@@ -2029,14 +2047,22 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
       ldx(c0 * kDenseChunk, xc);
 #pragma unroll
       for (int i = 0; i < MT; ++i) xn[i] = xc[i];
+      // this thread's part of a chunk's fragments, all its loads in flight at
+      // once; the next chunk's are loaded while the current one computes
+      constexpr int WV = kDenseChunk * NT * 64 / 256;
+      f16x8 wv[WV];
+      auto ldw = [&](int c) {
+        const f16x8* src = wsrc + (size_t)c * kDenseChunk * NT * 64 + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < WV; ++i) wv[i] = src[i * 256];
+      };
+      ldw(c0);
       for (int c = c0; c < c1; ++c) {
         __syncthreads();  // the previous chunk's fragments are read
-        {
-          const f16x8* src = wsrc + (size_t)c * kDenseChunk * NT * 64;
-          f16x8* dst = &wl[0][0][0];
-          for (int i = threadIdx.x; i < kDenseChunk * NT * 64; i += 256) dst[i] = src[i];
-        }
+#pragma unroll
+        for (int i = 0; i < WV; ++i) (&wl[0][0][0])[threadIdx.x + i * 256] = wv[i];
         __syncthreads();
+        if (c + 1 < c1) ldw(c + 1);
 #pragma unroll
         for (int j = 0; j < kDenseChunk; ++j) {
           const int ks = c * kDenseChunk + j;
@@ -2052,14 +2078,15 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
         }
       }
       if constexpr (!G) break;
-      // the next camera among the block's rows (uniform)
-      int64_t next = -1;
-      for (int r = 0; r < kDenseTileRows && next < 0; ++r) {
+      // the next camera among the block's rows (the same in every wave)
+      int next = INT_MAX;
+      for (int r = lane; r < kDenseTileRows; r += 64) {
         const int64_t u = blk * kDenseTileRows + r;
-        if (u < cnt && cam_of(u) > cam) next = cam_of(u);
+        const int c = u < cnt ? cam_at(a, u) : INT_MAX;
+        if (c > cam && c < next) next = c;
       }
-      if (next < 0) break;
-      cam = next;
+      cam = next_cam(next, cam);
+      if (cam == INT_MAX) break;
     }
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -2070,9 +2097,11 @@ __global__ void __launch_bounds__(256) k_dense_tiles(DenseArgs a, f32x4* __restr
 }
 
 // k_dense_finish: a workgroup per 16-survivor tile; its kDenseFinWaves waves
-// add interleaved subsets of the tile's K parts (wave w: parts w, w + 4, ...),
-// wave 0 adds the waves' sums in wave order and applies dense_out.
-constexpr int kDenseFinWaves = 4;
+// add interleaved subsets of the tile's K parts (wave w: parts w, w + 8, ...;
+// a call of few survivors has up to 72 parts, and each wave's chain of loads
+// is the kernel's time), then the waves' sums are added in wave order and
+// dense_out is applied, the cameras of a group's tile by a wave each.
+constexpr int kDenseFinWaves = 8;
 
 template <typename T, int NT, bool G>
 __global__ void __launch_bounds__(64 * kDenseFinWaves) k_dense_finish(DenseArgs a,
@@ -2085,61 +2114,66 @@ __global__ void __launch_bounds__(64 * kDenseFinWaves) k_dense_finish(DenseArgs 
   int64_t cnt = *a.count;
   if (cnt > a.max_count) cnt = a.max_count;
   const int64_t tiles = (cnt + 15) / 16;
+  constexpr int U = NT <= 8 ? 2 : 1;  // parts whose loads are in flight together
   const int kparts = a.tiled ? dense_tile_kparts(cnt, (a.flat + 31) / 32)
                              : dense_kparts(tiles, (a.flat + KS - 1) / KS);
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t s = tile * 16 + m;
+    const int mine = G && s < cnt ? cam_at(a, s) : INT_MAX;
     f32x4 t[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) t[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int kp = wave; kp < kparts; kp += kDenseFinWaves) {
+    for (int kp = wave; kp < kparts; kp += U * kDenseFinWaves) {
+      f32x4 v[U][NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) t[nt] += part[((tile * kparts + kp) * NT + nt) * 64 + lane];
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int k = kp + u * kDenseFinWaves;
+          v[u][nt] = k < kparts ? part[((tile * kparts + k) * NT + nt) * 64 + lane]
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) t[nt] += v[u][nt];
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = t[nt];
     __syncthreads();
-    if (wave == 0) {
+    for (int nt = wave; nt < NT; nt += kDenseFinWaves) {
+      f32x4 u = red[0][nt][lane];
+#pragma unroll
+      for (int w = 1; w < kDenseFinWaves; ++w) u += red[w][nt][lane];
+      red[0][nt][lane] = u;  // this lane's own slot
+    }
+    __syncthreads();
+    // one pass per camera among the rows (one without a camera group), the
+    // passes dealt over the waves
+    int cam = G ? next_cam(mine, -1) : 0;
+    for (int pass = 0; cam != INT_MAX; ++pass, cam = G ? next_cam(mine, cam) : INT_MAX) {
+      if (pass % kDenseFinWaves != wave) continue;
+      int64_t off = 0;
+      float b2 = a.b2;
+      double c_low = a.c_low, c_high = a.c_high;
+      if constexpr (G) {
+        const CamNet& cn = a.nets[cam];
+        off = cn.woff;
+        b2 = cn.b2;
+        c_low = cn.c_low;
+        c_high = cn.c_high;
+      }
+      // fp16 path: the camera's output scale (a row's partial sums hold only
+      // its own camera's products, and this pass writes only that camera's rows)
+      const float sc = Elt<T>::CVT ? at_off(a.scl, off)[1] : 1.0f;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         t[nt] = red[0][nt][lane];
-#pragma unroll
-        for (int w = 1; w < kDenseFinWaves; ++w) t[nt] += red[w][nt][lane];
+        if constexpr (Elt<T>::CVT) t[nt] *= sc;
       }
-      int64_t cam = G ? a.idx[tile * 16] / a.per_cam : 0;
-      for (;;) {
-        int64_t off = 0;
-        float b2 = a.b2;
-        double c_low = a.c_low, c_high = a.c_high;
-        if constexpr (G) {
-          const CamNet& cn = a.nets[cam];
-          off = cn.woff;
-          b2 = cn.b2;
-          c_low = cn.c_low;
-          c_high = cn.c_high;
-        }
-        if constexpr (Elt<T>::CVT) {
-          // the camera's output scale (a row's partial sums hold only its own
-          // camera's products, and this pass writes only that camera's rows)
-          f32x4 u[NT];
-          const float sc = at_off(a.scl, off)[1];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) u[nt] = t[nt] * sc;
-          dense_out<NT, G>(a, u, at_off(a.b1, off), at_off(a.w2, off), b2, c_low, c_high,
-                           tile * 16, cnt, cam, m, g);
-        } else {
-          dense_out<NT, G>(a, t, at_off(a.b1, off), at_off(a.w2, off), b2, c_low, c_high,
-                           tile * 16, cnt, cam, m, g);
-        }
-        if constexpr (!G) break;
-        int64_t next = -1;
-        for (int r = 0; r < 16 && next < 0; ++r) {
-          const int64_t u = tile * 16 + r;
-          if (u < cnt && a.idx[u] / a.per_cam > cam) next = a.idx[u] / a.per_cam;
-        }
-        if (next < 0) break;
-        cam = next;
-      }
-    }  // wave 0
+      dense_out<NT, G>(a, t, at_off(a.b1, off), at_off(a.w2, off), b2, c_low, c_high, tile * 16,
+                       cnt, cam, m, g);
+    }
     __syncthreads();  // red is read before the next tile writes it
   }
 }
@@ -2757,6 +2791,7 @@ int run_cnn(const Cnn& cnn, const CnnRunArgs& r, void* ws, size_t ws_bytes, hipS
     int64_t grid_fin = tiles;  // a workgroup per tile
     if (grid_fin > kNumCU * 4) grid_fin = kNumCU * 4;
     if (grid_fin < 1) grid_fin = 1;
+    d.w1 = cnn.h16 ? cnn.w1f : d.w1;
     if (cnn.h16)
       return launch_dense_split_nt<_Float16>(nt, d, part, (unsigned)grid_part, (unsigned)grid_fin,
                                              stream);

@@ -118,3 +118,25 @@ def test_compaction_forms(n, shift):
         assert int(cnt.item()) == want.size
         assert np.array_equal(idx.cpu().numpy()[:want.size], want)
         assert (idx.cpu().numpy()[want.size:] == -7).all()
+
+
+@pytest.mark.parametrize("cams,n", [(20, 1), (40, 2), (3, 50)])
+def test_group_tiles_of_many_cameras(cams, n):
+    """Tiles of 16 survivors that hold up to 16 cameras' rows, each row with
+    its camera's dense layer and thresholds: logits as in the camera's own
+    cascade, up to the order of the dense layer's fp32 sums (256 products of
+    fp16 values, a few 2^-24 each of their magnitude)."""
+    wls = [_workload(1) for _ in range(cams)]
+    blobs = [_blob(c) for c in range(cams)]
+    videos = [_frames(n, c) for c in range(cams)]
+    group = GroupRunner(wls, blobs, n)
+    group.run(torch.cat(videos), n, t0=0)
+    for c in range(cams):
+        r = CascadeRunner(wls[c], blobs[c], n)
+        r.run(videos[c], n, t0=0)
+        got, want = group.logit[c * n:(c + 1) * n], r.logit[:n]
+        assert torch.equal(torch.isnan(got), torch.isnan(want))
+        fired = ~torch.isnan(want)
+        assert torch.allclose(got[fired], want[fired], rtol=1e-5, atol=1e-5)
+        r.close()
+    group.close()
