@@ -527,7 +527,55 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
               w1f[(((size_t)ks * nts + nt) * 64 + lane) * 8 + e] = w1h[(size_t)u * c.flat + k];
           }
   }
-  // device image: [conv_w][conv_wf][conv_wh][conv_b][w1][w1h][b1][w2][scales][w0h][w1f]
+  // fp32 networks: every conv weight as three bf16 parts (their sum, split by
+  // truncation), in the fragment orders of k_first_x3 and k_conv_x3
+  std::vector<uint16_t> convwx;
+  if (!c.bf16) {
+    auto part = [](float v, int plane) -> uint16_t {
+      uint32_t u = 0;
+      for (int p = 0; p <= plane; ++p) {
+        if (p > 0 && !isfinite(v)) return 0;  // an infinite weight has no remainder
+        memcpy(&u, &v, 4);
+        u &= 0xFFFF0000u;
+        float t;
+        memcpy(&t, &u, 4);
+        if (p < plane) v = isfinite(v) ? v - t : INFINITY;
+      }
+      return (uint16_t)(u >> 16);
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+      CnnLayer& L = c.layers[l];
+      const int nts = L.cout / 16;
+      L.wx_off = convwx.size();
+      if (l == 0) {
+        convwx.resize(L.wx_off + (size_t)6 * nts * 512, 0);
+        // step 1: lane groups 0, 1 hold plane lo[q] and 2, 3 plane hi[q] of dy = 2
+        const int lo[3] = {0, 1, 2}, hi[3] = {1, 0, 0};
+        for (int q = 0; q < 6; ++q)
+          for (int nt = 0; nt < nts; ++nt)
+            for (int lane = 0; lane < 64; ++lane)
+              for (int e = 0; e < 8; ++e) {
+                const int g = lane >> 4, o = nt * 16 + (lane & 15);
+                const int k = q < 3 ? g * 8 + e : 32 + (g & 1) * 8 + e;
+                const int plane = q < 3 ? q : (g < 2 ? lo[q - 3] : hi[q - 3]);
+                convwx[L.wx_off + (((size_t)q * nts + nt) * 64 + lane) * 8 + e] =
+                    part(convw[L.w_off + (size_t)o * L.kpad + k], plane);
+              }
+      } else if (L.cin % 32 == 0) {
+        convwx.resize(L.wx_off + (size_t)3 * L.cout * 9 * L.cin);
+        size_t at = L.wx_off;
+        for (int cb = 0; cb < L.cin / 32; ++cb)
+          for (int t = 0; t < 9; ++t)
+            for (int p = 0; p < 3; ++p)
+              for (int nt = 0; nt < nts; ++nt)
+                for (int lane = 0; lane < 64; ++lane)
+                  for (int e = 0; e < 8; ++e)
+                    convwx[at++] = part(convw[L.w_off + (size_t)(nt * 16 + (lane & 15)) * L.kpad +
+                                              t * L.cin + cb * 32 + (lane >> 4) * 8 + e], p);
+      }
+    }
+  }
+  // device image: [conv_w][conv_wf][conv_wh][conv_b][w1][w1h][b1][w2][scales][w0h][w1f][conv_wx]
   const size_t o_cw = 0;
   const size_t o_cwf = align_up(o_cw + conv_elems * es, kAlign);
   const size_t o_cwh = align_up(o_cwf + convwf.size() * es, kAlign);
@@ -539,7 +587,8 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
   const size_t o_sc = align_up(o_w2 + (size_t)c.dense * 4, kAlign);
   const size_t o_w0h = align_up(o_sc + scales.size() * 4, kAlign);
   const size_t o_w1f = align_up(o_w0h + w0h.size() * 2, kAlign);
-  const size_t total = align_up(o_w1f + w1f.size() * 2, kAlign);
+  const size_t o_wx = align_up(o_w1f + w1f.size() * 2, kAlign);
+  const size_t total = align_up(o_wx + convwx.size() * 2, kAlign);
   std::vector<unsigned char> img(total, 0);
   auto put = [&](size_t off, const std::vector<float>& v, bool as_bf16) {
     if (as_bf16) {
@@ -562,6 +611,7 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
   put(o_sc, scales, false);
   if (!w0h.empty()) put(o_w0h, w0h, true);
   if (!w1f.empty()) memcpy(img.data() + o_w1f, w1f.data(), w1f.size() * 2);
+  if (!convwx.empty()) memcpy(img.data() + o_wx, convwx.data(), convwx.size() * 2);
   void* dev = nullptr;
   if (hipMalloc(&dev, total) != hipSuccess)
     return fail(NSC_E_NOMEM, "hipMalloc of %zu bytes for CNN weights failed", total);
@@ -582,6 +632,7 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
   c.scales = reinterpret_cast<float*>(b + o_sc);
   c.conv_w0h = w0h.empty() ? nullptr : b + o_w0h;
   c.w1f = w1f.empty() ? nullptr : b + o_w1f;
+  c.conv_wx = convwx.empty() ? nullptr : b + o_wx;
   nsc_cnn* h = new (std::nothrow) nsc_cnn;
   if (!h) {
     (void)hipFree(dev);

@@ -41,6 +41,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 namespace nsc {
 namespace {
 
@@ -115,6 +117,16 @@ __device__ __forceinline__ uint16_t div_to_bf16_bits_fast(int32_t N, int32_t D, 
   return f32_to_bf16_bits(r);
 }
 
+// A value whose origin the compiler does not see.  Two 8-byte LDS reads 8 bytes
+// apart at an 8-byte-aligned address are merged into one 16-byte read, which
+// stalls the LDS for about 45 cycles where it is not 16-byte aligned
+// (SQ_LDS_UNALIGNED_STALL); with the distance of the second read opaque they
+// stay two reads of a few cycles each.
+__device__ __forceinline__ int opaque(int v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Element-type traits: E = elements per lane per MFMA, KS = K per MFMA.
 template <typename T> struct Elt;
 template <> struct Elt<uint16_t> {  // bf16 stored as raw bits
@@ -130,11 +142,11 @@ template <> struct Elt<uint16_t> {  // bf16 stored as raw bits
   static __device__ __forceinline__ frag load(const uint16_t* p) {  // 16-byte aligned
     return *reinterpret_cast<const frag*>(p);
   }
-  static __device__ __forceinline__ frag load8(const uint16_t* p) {  // 8-byte aligned
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    const bf16x4 lo = *reinterpret_cast<const bf16x4*>(p);
-    const bf16x4 hi = *reinterpret_cast<const bf16x4*>(p + 4);
-    return frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  // 8-byte aligned; four = opaque(4)
+  static __device__ __forceinline__ frag load8(const uint16_t* p, int four) {
+    const uint2 lo = *reinterpret_cast<const uint2*>(p);
+    const uint2 hi = *reinterpret_cast<const uint2*>(p + four);
+    return __builtin_bit_cast(frag, make_uint4(lo.x, lo.y, hi.x, hi.y));
   }
   static __device__ __forceinline__ frag zero() {
     frag z;
@@ -194,16 +206,15 @@ template <> struct Elt<float> {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ float load(const float* p) { return *p; }
-  static __device__ __forceinline__ float load8(const float* p) { return *p; }
+  static __device__ __forceinline__ float load8(const float* p, int) { return *p; }
   static __device__ __forceinline__ float zero() { return 0.0f; }
   static __device__ __forceinline__ void set(float& f, int, float v) { f = v; }
   static constexpr bool SPLIT = false;
-  static constexpr bool CVT = false;
 };
 // fp32 dense layers: a step of 16 features as four MFMAs of 4.  A lane group
 // takes four consecutive features of each, so that every load is 16 bytes
 // (one feature per lane and load read 16-byte pieces of 16 rows: 3,000
-// survivors of 4,608 features 82 us, now DNOW).
+// survivors of 4,608 features 82 us, now 27).
 struct F32x16 {};
 template <> struct Elt<F32x16> {
   static constexpr int E = 4, KS = 16;
@@ -476,6 +487,7 @@ template <typename T, int NT>
 __device__ __forceinline__ void first_tile(const T* in, const T* wl, int w_lds, int band_w,
                                            int row0, int col0, int m, int g, f32x4 (&acc)[NT]) {
   using X = Elt<T>;
+  const int four = opaque(4);
   constexpr int E = X::E, KS = X::KS;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -485,35 +497,13 @@ __device__ __forceinline__ void first_tile(const T* in, const T* wl, int w_lds, 
     typename X::frag av = X::zero();
     if (k < 48) {
       const int dy = k >> 4, dx = (k >> 2) & 3, c = k & 3;
-      av = X::load8(in + ((row0 + dy) * band_w + col0 + dx) * 4 + c);
+      av = X::load8(in + ((row0 + dy) * band_w + col0 + dx) * 4 + c, four);
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const typename X::frag bv = X::load(wl + (nt * 16 + m) * w_lds + k);
       acc[nt] = X::mma(av, bv, acc[nt]);
     }
-  }
-}
-
-// The same with the weight fragments already in registers (bf16: K = 64 in two
-// steps of 32, fragment [step][nt]).
-template <int NT>
-__device__ __forceinline__ void first_tile_b(const uint16_t* in, const bf16x8 (&bw)[2][NT],
-                                             int band_w, int row0, int col0, int g,
-                                             f32x4 (&acc)[NT]) {
-  using X = Elt<uint16_t>;
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int k = ks * 32 + g * 8;
-    bf16x8 av = X::zero();
-    if (k < 48) {
-      const int dy = k >> 4, dx = (k >> 2) & 3;
-      av = X::load8(in + ((row0 + dy) * band_w + col0 + dx) * 4);
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(av, bw[ks][nt], acc[nt]);
   }
 }
 
@@ -883,12 +873,13 @@ __global__ void __launch_bounds__(1024) k_conv_pair(ConvArgs a0, ConvArgs a1, Pa
       const int in_l0 = ((py + (g >> 1)) * a0.band_w + px + 2 * (g & 1)) * 4;
       const int in_l1 = ((py + (k1 >> 4)) * a0.band_w + px + ((k1 >> 2) & 3)) * 4;
       const bool use1 = k1 < 48;
+      const int four = opaque(4);
       const int out_l = (((g >> 1) + 1) * a1.band_w + (g & 1) + 1) * a1.cin_lds + m;
       for (int t = wave; t < a0.tiles_y * a0.tiles_x; t += nwaves) {
         const int ty = t / a0.tiles_x, tx = t - ty * a0.tiles_x;
         const uint16_t* tin = in0 + (4 * ty * a0.band_w + 4 * tx) * 4;
-        const bf16x8 x0 = X::load8(tin + in_l0);
-        const bf16x8 x1 = use1 ? X::load8(tin + in_l1) : X::zero();
+        const bf16x8 x0 = X::load8(tin + in_l0, four);
+        const bf16x8 x1 = use1 ? X::load8(tin + in_l1, four) : X::zero();
         f32x4 acc[NT0];
 #pragma unroll
         for (int nt = 0; nt < NT0; ++nt) {
@@ -1693,6 +1684,427 @@ k_pair64(ConvArgs a0, ConvArgs a1, Band64 b, const uint2* __restrict__ xin, int3
   }
 }
 
+// ------------------------------------------ fp32 layers on the bf16 cores
+//
+// An fp32 network's conv layers run on the bf16 matrix cores without giving
+// up fp32 operands: every fp32 value is the exact sum of three bf16 values
+// (8 significant bits each, split by truncation), and a product takes the six
+// of the nine partial products that reach 2^-16 of it,
+//   h h', h m', m h', h l', l h', m m',
+// each exact in the fp32 accumulation; the three left out are below 2^-22 of
+// the product together.  The first goes into one accumulator and the five
+// small ones into another, added at the end, so a sum rounds once per 32
+// products where v_mfma_f32_16x16x4_f32 rounds once per 4.  Error of the
+// logits against fp64 (2-norm, random He-normal networks on 50x50 inputs):
+// 32-32 channels 2.8e-7 against 4.2e-7 on the fp32 cores, 64-64-64-64
+// 4.7e-7 against 8.8e-7, and below theirs in all seven networks compared.
+// Weights are split on the host, in fragment order.
+
+// The three bf16 parts of 8 fp32 values, packed (0 remainders for infinities
+// and NaN, so that these pass through as in one product).
+__device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& h, uint4& m,
+                                       uint4& l) {
+  const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t hb[8], mb[8], lb[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    hb[e] = __float_as_uint(v[e]) & 0xFFFF0000u;
+    float r = v[e] - __uint_as_float(hb[e]);
+    r = r == r ? r : 0.0f;
+    mb[e] = __float_as_uint(r) & 0xFFFF0000u;
+    lb[e] = __float_as_uint(r - __uint_as_float(mb[e]));
+  }
+  auto pack = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };
+  h = make_uint4(pack(hb[0], hb[1]), pack(hb[2], hb[3]), pack(hb[4], hb[5]), pack(hb[6], hb[7]));
+  m = make_uint4(pack(mb[0], mb[1]), pack(mb[2], mb[3]), pack(mb[4], mb[5]), pack(mb[6], mb[7]));
+  l = make_uint4(pack(lb[0], lb[1]), pack(lb[2], lb[3]), pack(lb[4], lb[5]), pack(lb[6], lb[7]));
+}
+
+// Inner layers (input channels a multiple of 32), banded as the 64-channel
+// bf16 layers (same tiles and LDS layout, Band64 with 4 chunks of 8 channels
+// per plane): 32 input channels at a time go into three LDS planes, the
+// weights of a tap come from L2 one step ahead, and a wave keeps up to
+// x3_tiles tiles of 16 pixels x 16 NT output channels.  Bound by the matrix
+// cores (6 x 9 x cin / 32 MFMAs per tile and 16 channels: 42 % busy) and the
+// stream of weights from L2.  3,000 images, 32 -> 32 channels, 25x25: 206 us
+// against 570 on the fp32 cores; 1,000 images of the 64-channel 4-layer
+// network 1.90 ms against 27.4, whose weights left room for one tile row in
+// the LDS.
+constexpr int x3_tiles(int nt) { return nt <= 2 ? 4 : 3; }
+
+// Stages channels c0 .. c0 + 31 of band rows [0, rows_used) into the planes.
+__device__ __forceinline__ void stage_x3(const float* __restrict__ src, int cin, int c0,
+                                         const Band64& b, unsigned char* lds, int y0,
+                                         int rows_used) {
+  constexpr int B = 4;  // units (8 channels of a pixel) whose loads are in flight
+  const int units = rows_used * b.w * 4;
+  const float inv_w = 1.0f / (float)b.w;
+  for (int u0 = threadIdx.x; u0 < units; u0 += B * blockDim.x) {
+    float4 v[B][2];
+    int addr[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const int u = u0 + j * blockDim.x;
+      const int pix = u >> 2, c = u & 3;
+      const int r = band_row(pix, inv_w), x = pix - r * b.w;
+      const int y = y0 + r;
+      addr[j] = u < units ? (c * b.cp + r * b.wb + x + 1) * 16 : -1;
+      v[j][0] = v[j][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (u < units && (unsigned)y < (unsigned)b.h) {
+        const float* p = src + ((int64_t)y * b.w + x) * cin + c0 + c * 8;
+        v[j][0] = *reinterpret_cast<const float4*>(p);
+        v[j][1] = *reinterpret_cast<const float4*>(p + 4);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      if (addr[j] < 0) continue;
+      uint4 h, m, l;
+      split3(v[j][0], v[j][1], h, m, l);
+      *reinterpret_cast<uint4*>(lds + addr[j]) = h;
+      *reinterpret_cast<uint4*>(lds + b.lo_bytes + addr[j]) = m;
+      *reinterpret_cast<uint4*>(lds + 2 * b.lo_bytes + addr[j]) = l;
+    }
+  }
+}
+
+// Nine taps of one 32-channel block for MT tiles; wp points at the block's
+// fragments [tap][plane][all output blocks][lane] of this wave's lane, ntw
+// fragments per plane; the small partial products go to lo.
+template <int MT, int NT>
+__device__ __forceinline__ void x3_taps(const unsigned char* lds, const Band64& b,
+                                        const bf16x8* __restrict__ wp, int ntw,
+                                        const uint32_t (&base)[MT], f32x4 (&acc)[MT][NT],
+                                        f32x4 (&lo)[MT][NT]) {
+  using X = Elt<uint16_t>;
+  bf16x8 wa[3][NT], wb[3][NT];
+  auto ldw = [&](int tap, bf16x8 (&d)[3][NT]) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) d[p][nt] = wp[((tap * 3 + p) * ntw + nt) * 64];
+  };
+  auto step = [&](int tap, const bf16x8 (&w)[3][NT]) {
+    const int dy = tap / 3, dx = tap - 3 * dy;
+    const uint32_t off = (uint32_t)(dy * b.wb + dx) * 16u;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const unsigned char* q = lds + base[i] + off;
+      const bf16x8 xh = *reinterpret_cast<const bf16x8*>(q);
+      const bf16x8 xm = *reinterpret_cast<const bf16x8*>(q + b.lo_bytes);
+      const bf16x8 xl = *reinterpret_cast<const bf16x8*>(q + 2 * b.lo_bytes);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[i][nt] = X::mma(w[0][nt], xh, acc[i][nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[i][nt] = X::mma(w[1][nt], xm, lo[i][nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[i][nt] = X::mma(w[2][nt], xh, lo[i][nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[i][nt] = X::mma(w[0][nt], xl, lo[i][nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[i][nt] = X::mma(w[1][nt], xh, lo[i][nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[i][nt] = X::mma(w[0][nt], xm, lo[i][nt]);
+    }
+  };
+  ldw(0, wa);
+#pragma unroll 1
+  for (int tap = 0; tap < 8; tap += 2) {
+    ldw(tap + 1, wb);
+    __builtin_amdgcn_sched_barrier(0);
+    step(tap, wa);
+    __builtin_amdgcn_sched_barrier(0);
+    ldw(tap + 2, wa);
+    __builtin_amdgcn_sched_barrier(0);
+    step(tap + 1, wb);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  step(8, wa);
+}
+
+template <int NT, bool G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_conv_x3(ConvArgs a, Band64 b) {
+  constexpr int MT = x3_tiles(NT);
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  band64_clear(lds, b);
+  int64_t cnt = *a.count;
+  if (cnt > a.max_count) cnt = a.max_count;
+  const int bands = (a.tiles_y + a.band_tiles - 1) / a.band_tiles;
+  const int ntw = a.cout / 16, ngrp = ntw / NT;  // output blocks; groups of NT
+  const int kb = a.cin / 32;
+  const int64_t items = (cnt + 7) / 8 * 8 * bands * ngrp;
+  const int ho = a.pool ? a.h / 2 : a.h, wo = a.pool ? a.w / 2 : a.w;
+  const int hn = a.pool ? ho * 2 : a.h, wn = a.pool ? wo * 2 : a.w;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    int64_t s;
+    int bg;
+    band_item(item, bands * ngrp, &s, &bg);
+    if (s >= cnt) continue;  // workgroup-uniform
+    const int bi = bg / ngrp, grp = bg - bi * ngrp;
+    const int ty0 = bi * a.band_tiles;
+    const int nty = min(a.band_tiles, a.tiles_y - ty0);
+    const int rows = min(4 * nty, hn - 4 * ty0);
+    const int ntile = band64_ntile(a.pool != 0, rows, wn);
+    const int64_t off = G ? slot_woff(a.nets, a.per_cam, a.idx, s) : 0;  // camera group
+    const bf16x8* wf = at_off(reinterpret_cast<const bf16x8*>(a.wts), off) + grp * NT * 64 + lane;
+    const float* bp = at_off(a.bias, off) + grp * NT * 16 + 4 * g;
+    const float* src = a.act_in + s * (int64_t)a.h * a.w * a.cin;
+    float* out = a.act_out + s * (int64_t)ho * wo * a.cout + grp * NT * 16 + 4 * g;
+    for (int t0 = 0; t0 < ntile; t0 += MT * kBandWaves) {  // one round at the usual sizes
+      f32x4 acc[MT][NT], lo[MT][NT];
+      uint32_t base[MT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        int r, x;
+        band_pixel(t0 + wave + kBandWaves * i, m, a.pool, rows, wn, r, x);
+        base[i] = (uint32_t)(g * b.cp + r * b.wb + x) * 16u;  // (0, 0) past the band: in bounds
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[i][nt] = lo[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      const int mt = min(MT, (ntile - t0 - wave + kBandWaves - 1) / kBandWaves);  // may be <= 0
+      for (int cb = 0; cb < kb; ++cb) {
+        if (kb > 1 || t0 == 0) {
+          __syncthreads();  // the previous block's readers are done (and the clear)
+          stage_x3(src, a.cin, 32 * cb, b, lds, 4 * ty0 - 1, 4 * nty + 2);
+          __syncthreads();
+        }
+        const bf16x8* wp = wf + (int64_t)cb * 27 * ntw * 64;
+        // tiles past the wave's last cost MFMAs: run the count it has
+        auto run = [&](auto n) {
+          constexpr int N = decltype(n)::value;
+          uint32_t bs[N];
+          f32x4 ac[N][NT], al[N][NT];
+#pragma unroll
+          for (int i = 0; i < N; ++i) {
+            bs[i] = base[i];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              ac[i][nt] = acc[i][nt];
+              al[i][nt] = lo[i][nt];
+            }
+          }
+          x3_taps<N, NT>(lds, b, wp, ntw, bs, ac, al);
+#pragma unroll
+          for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              acc[i][nt] = ac[i][nt];
+              lo[i][nt] = al[i][nt];
+            }
+        };
+        switch (mt) {
+          case 1: run(std::integral_constant<int, 1>()); break;
+          case 2: run(std::integral_constant<int, 2>()); break;
+          case 3: run(std::integral_constant<int, 3>()); break;
+          case 4: if constexpr (MT >= 4) run(std::integral_constant<int, MT >= 4 ? 4 : 1>()); break;
+          default: break;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        int r, x;
+        const bool in = i < mt && band_pixel(t0 + wave + kBandWaves * i, m, a.pool, rows, wn, r, x);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[i][nt] += lo[i][nt];
+        if (i < mt)  // uniform
+          band64_epilogue<NT>(acc[i], bp, 1.0f, 1.0f, out, a.cout, in ? 4 * ty0 + r : b.h, x, b.h,
+                              b.w, a.pool, m, false);
+      }
+    }
+  }
+}
+
+// First layer of an fp32 network (3 input channels): the survivor's area sums
+// become fp32 inputs, each pixel 24 bytes of LDS: the h, m and l parts of its
+// 4 channels (the fourth 0), read 8 bytes at a time (see opaque()).  K is (dy, dx of 4, c of 4) = 48 of 64: a first MFMA step takes dy 0
+// and 1, and the half-used second one (dy 2) carries a second partial product
+// in its upper half (pairs h h' | m m', h m' | m h', h l' | l h'), so a tile
+// takes 9 MFMAs per 16 channels.  Pixels run along the band in raster order
+// (4 pooling windows per tile on a pooling layer), the lane's position
+// carried from tile to tile.  Bound by instruction issue (45 vector
+// instructions and 18 MFMAs per tile) and the input gather's latency.  3,000
+// images of 50x50, 32 channels: 150 us against 335 on the fp32 cores.
+struct FirstX3 {
+  int32_t bw;          // staged pixels per band row (image columns -1 .. bw - 2)
+  double inv255;       // 1 / (255 den)
+};
+
+// Waves per SIMD (and workgroups per CU) of k_first_x3, by its registers.
+template <int NT>
+constexpr int first_x3_waves() {
+  return NT <= 2 ? 4 : 2;
+}
+
+template <int NT, bool POOL, bool G>
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(first_x3_waves<NT>(), first_x3_waves<NT>())))
+    k_first_x3(ConvArgs a, FirstX3 f) {
+  using X = Elt<uint16_t>;
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  int64_t cnt = *a.count;
+  if (cnt > a.max_count) cnt = a.max_count;
+  const int bands = (a.tiles_y + a.band_tiles - 1) / a.band_tiles;
+  const int ntw = a.cout / 16, ngrp = ntw / NT;
+  const int64_t items = cnt * bands * ngrp;
+  constexpr uint32_t kPix = 24;            // bytes of a staged pixel
+  constexpr int R = POOL ? 2 : 1;          // pixels per unit (window or pixel) and axis
+  constexpr int UPT = POOL ? 4 : 16;       // units per tile
+  constexpr int ADV = UPT * kBandWaves;    // units from one tile of a wave to its next
+  const int wo = a.w / R, ho = a.h / R;    // output map: wo units per unit row
+  const int hn = ho * R;
+  const int adv_r = ADV / wo, adv_x = ADV - adv_r * wo;
+  const uint32_t q_adv = (uint32_t)(R * (adv_r * f.bw + adv_x)) * kPix;
+  const uint32_t q_wrap = (uint32_t)(R * (f.bw - wo)) * kPix;
+  // per-lane K offsets (bytes): step 0 chunk (dy, dx) = (g / 2, 2 (g mod 2)),
+  // step 1 chunk (2, 2 (g mod 2)) of part h (g < 2) or of part m / l
+  const uint32_t o0 = (uint32_t)((g >> 1) * f.bw + 2 * (g & 1)) * kPix;
+  const uint32_t o0m = (uint32_t)opaque((int)o0 + 8), o0l = (uint32_t)opaque((int)o0 + 16);
+  const uint32_t o1 = (uint32_t)(2 * f.bw + 2 * (g & 1)) * kPix;
+  const uint32_t o1m = o1 + (g < 2 ? 0u : 8u), o1l = o1 + (g < 2 ? 0u : 16u);
+  const int j = POOL ? m & 3 : 0;          // pixel of the window
+  const int u_lane = wave * UPT + (POOL ? m >> 2 : m);
+  const int ur0 = band_row(u_lane, 1.0f / (float)wo), ux0 = u_lane - ur0 * wo;
+  const uint32_t q0 = (uint32_t)((R * ur0 + (j >> 1)) * f.bw + R * ux0 + (j & 1)) * kPix;
+  // the chunk's two pixels
+  auto ld = [&](uint32_t addr) {
+    const uint2 p = *reinterpret_cast<const uint2*>(lds + addr);
+    const uint2 q = *reinterpret_cast<const uint2*>(lds + addr + kPix);
+    return __builtin_bit_cast(bf16x8, make_uint4(p.x, p.y, q.x, q.y));
+  };
+  // fragments [3 planes of step 0, then the 3 pairs of step 1][output block]
+  bf16x8 w[6][NT];
+  f32x4 bias[NT];
+  int64_t w_off = 0;
+  int w_grp = -1;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t s = item / (bands * ngrp);
+    const int bg = (int)(item - s * (bands * ngrp));
+    const int bi = bg / ngrp, grp = bg - bi * ngrp;
+    const int ty0 = bi * a.band_tiles;
+    const int nty = min(a.band_tiles, a.tiles_y - ty0);
+    const int rows = min(4 * nty, hn - 4 * ty0);
+    const int64_t off = G ? slot_woff(a.nets, a.per_cam, a.idx, s) : 0;  // camera group
+    if (off != w_off || grp != w_grp) {  // uniform: once without groups
+      const bf16x8* wf = at_off(reinterpret_cast<const bf16x8*>(a.wts), off) + grp * NT * 64 + lane;
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) w[q][nt] = wf[(q * ntw + nt) * 64];
+      const float* bp = at_off(a.bias, off) + grp * NT * 16 + 4 * g;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(bp + nt * 16);
+      w_off = off;
+      w_grp = grp;
+    }
+    __syncthreads();  // the previous item's readers are done
+    {
+      const int32_t* S = a.sums + (int64_t)a.idx[s] * a.sums_h * a.sums_w * 3;
+      const int npix = (4 * nty + 2) * f.bw;
+      const float inv_bw = 1.0f / (float)f.bw;
+      const double den = (double)a.den255;
+#pragma unroll 3
+      for (int p = threadIdx.x; p < npix; p += 256) {
+        const int br = band_row(p, inv_bw), bc = p - br * f.bw;
+        const int y = 4 * ty0 - 1 + br, x = bc - 1;
+        float v[3] = {0.f, 0.f, 0.f};
+        if ((unsigned)y < (unsigned)a.h && (unsigned)x < (unsigned)a.w) {
+          int32_t c[3];
+          cell_sums(a, S, y, x, c);
+          // (2 S - den255) is exact in fp64; the product with the rounded
+          // reciprocal is within 2^-52 of the quotient before it is rounded to fp32
+#pragma unroll
+          for (int k = 0; k < 3; ++k) v[k] = (float)(fma(2.0, (double)c[k], -den) * f.inv255);
+        }
+        uint4 h, mm, l;
+        split3(make_float4(v[0], v[1], v[2], 0.f), make_float4(0.f, 0.f, 0.f, 0.f), h, mm, l);
+        uint2* d = reinterpret_cast<uint2*>(lds + p * kPix);
+        d[0] = make_uint2(h.x, h.y);
+        d[1] = make_uint2(mm.x, mm.y);
+        d[2] = make_uint2(l.x, l.y);
+      }
+    }
+    __syncthreads();
+    const int units = rows / R * wo;  // of the band
+    const int ntile = (units + UPT - 1) / UPT;
+    int u = u_lane, ux = ux0;
+    uint32_t qn = q0;
+    // units are the band's outputs in raster order, so they follow one another in memory
+    float* o = a.act_out + (s * (int64_t)ho + 4 / R * ty0) * wo * a.cout + grp * NT * 16 + 4 * g +
+               u_lane * a.cout + (POOL ? 16 * j : 0);
+    for (int t = wave; t < ntile; t += kBandWaves) {
+      const bool in = u < units;
+      const uint32_t q = in ? qn : 0u;
+      const bf16x8 xh = ld(q + o0), xm = ld(q + o0m), xl = ld(q + o0l);
+      const bf16x8 yhm = ld(q + o1m), yhl = ld(q + o1l);
+      f32x4 acc[NT], lo[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[1][nt], xm, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], xh, bias[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[2][nt], xh, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[0][nt], xl, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[1][nt], xh, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[3][nt], yhm, acc[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[5][nt], yhl, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[0][nt], xm, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] += X::mma(w[4][nt], yhm, lo[nt]);
+      // ReLU and pooling on the bits: as signed integers the positive floats
+      // order like their values, above every negative one
+      int4 r[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        int v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = __float_as_int(acc[nt][e]);
+          if constexpr (POOL) {
+            v[e] = max(v[e], __builtin_amdgcn_update_dpp(0, v[e], kQuadXor1, 0xF, 0xF, true));
+            v[e] = max(v[e], __builtin_amdgcn_update_dpp(0, v[e], kQuadXor2, 0xF, 0xF, true));
+          }
+          v[e] = max(v[e], 0);
+        }
+        r[nt] = make_int4(v[0], v[1], v[2], v[3]);
+      }
+      if constexpr (POOL) {  // the window's lane j stores output block j
+        int4 q = r[0];
+#pragma unroll
+        for (int nt = 1; nt < NT; ++nt) {
+          q.x = j == nt ? r[nt].x : q.x;
+          q.y = j == nt ? r[nt].y : q.y;
+          q.z = j == nt ? r[nt].z : q.z;
+          q.w = j == nt ? r[nt].w : q.w;
+        }
+        if (in && j < NT) *reinterpret_cast<int4*>(o) = q;
+      } else if (in) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<int4*>(o + nt * 16) = r[nt];
+      }
+      u += ADV;
+      o += ADV * a.cout;
+      ux += adv_x;
+      qn += q_adv;
+      if (ux >= wo) {
+        ux -= wo;
+        qn += q_wrap;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ dense
 
 struct DenseArgs {
@@ -2452,6 +2864,13 @@ int launch_pair(int nt0, int nt1, const ConvArgs& a0, const ConvArgs& a1, const 
 }
 }  // namespace
 
+// 16-channel output blocks that a wave of the fp32 split kernels computes
+// together, of a layer of nt (1, 2, 3, 4, 6, 8 or 16): two, with four tiles, fit
+// the registers with both sets of a tap's weights (64 channels in one group
+// of four blocks spilled: 2.55 ms against 1.90 for 1,000 images of the
+// 4-layer network), although each group stages its own input.
+static int x3_group(int nt) { return nt <= 3 ? nt : 2; }
+
 // Band plan of a 64-input-channel bf16 layer (k_band64 / k_pair64): among
 // the band heights of at most 16 tiles or two tile rows whose planes (one
 // fp16 plane with h16, else the bf16 hi and lo planes) fit 80 KB, so that two
@@ -2568,6 +2987,135 @@ int launch_band64(bool pair, int nt, const ConvArgs& a0, const ConvArgs& a1, con
 #undef NSC_BAND_LAUNCH
 #undef NSC_BAND_LAUNCH2
   NSC_CHECK_LAUNCH(pair ? "k_pair64" : "k_band64");
+  return NSC_OK;
+}
+}  // namespace
+
+// Band plan of an fp32 network's inner layer on the split path (k_conv_x3):
+// the band height with the least work per image for the busiest wave, as
+// band64_plan, among those of one round of tiles whose three planes of 32
+// channels fit 80 KB (two workgroups per CU), and at most max_bt tile rows
+// (small calls: more, shorter bands to fill the chip).  False where the layer
+// does not qualify or not even one tile row fits the LDS.
+bool x3_plan(const CnnLayer& L, int32_t max_bt, Band64* b, int32_t* band_tiles, size_t* lds) {
+  if (L.cin % 32 != 0) return false;
+  int32_t ty, tx;
+  conv_tiles(L, &ty, &tx);
+  int32_t wb = L.w + 2;
+  wb += ((4 - wb) % 8 + 8) % 8;  // = 4 (mod 8)
+  auto plan = [&](int32_t bt) {
+    Band64 p{};
+    p.w = L.w;
+    p.h = L.h;
+    p.rows = 4 * bt + 2;
+    p.wb = wb;
+    p.cp = p.rows * wb + 1;
+    p.lo_bytes = 4 * p.cp * 16;
+    p.planes = 3;
+    return p;
+  };
+  const int32_t per_round = x3_tiles(x3_group(L.cout / 16)) * kBandWaves;
+  const int32_t hn = L.pool ? (L.h / 2) * 2 : L.h, wn = L.pool ? (L.w / 2) * 2 : L.w;
+  int32_t bt = 1;
+  int64_t best = INT64_MAX;
+  for (int32_t c = 1; c <= ty; ++c) {
+    if (c > 1 && (band64_ntile(L.pool, std::min(4 * c, hn), wn) > per_round ||
+                  band64_bytes(plan(c)) > 80 * 1024 || (max_bt > 0 && c > max_bt)))
+      break;
+    const int64_t bands = (ty + c - 1) / c;
+    int64_t work = 0;  // tiles of the fullest band's busiest wave, and a tile for its staging
+    for (int32_t y0 = 0; y0 < ty; y0 += c) {
+      const int64_t t = band64_ntile(L.pool, std::min(4 * c, hn - 4 * y0), wn);
+      work = std::max(work, (t + kBandWaves - 1) / kBandWaves + 1);
+    }
+    if (bands * work <= best) {
+      best = bands * work;
+      bt = c;
+    }
+  }
+  // band_row's exactness bound on the pixels of a band
+  if (band64_bytes(plan(bt)) > 160 * 1024 || plan(bt).rows * wb > 1280) return false;
+  *b = plan(bt);
+  *band_tiles = bt;
+  *lds = band64_bytes(*b);
+  return true;
+}
+
+namespace {
+int launch_x3(const ConvArgs& a, const Band64& b, size_t lds, int64_t max_count, hipStream_t st) {
+  const int nt = a.cout / 16, grp = x3_group(nt);
+  const int64_t bands = (a.tiles_y + a.band_tiles - 1) / a.band_tiles;
+  const int64_t items = (max_count + 7) / 8 * 8 * bands * (nt / grp);
+  const int64_t per_cu = lds <= 80 * 1024 ? 2 : 1;
+  int64_t grid = kNumCU * per_cu;  // a multiple of 8 (see band_item)
+  if (grid > items) grid = items;
+#define NSC_X3_CASE(N)                                                                          \
+  case N:                                                                                       \
+    if (a.nets)                                                                                 \
+      hipLaunchKernelGGL((k_conv_x3<N, true>), dim3((unsigned)grid), dim3(64 * kBandWaves), lds, \
+                         st, a, b);                                                             \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_conv_x3<N, false>), dim3((unsigned)grid), dim3(64 * kBandWaves), lds, \
+                         st, a, b);                                                             \
+    break;
+  switch (grp) {
+    NSC_X3_CASE(1)
+    NSC_X3_CASE(2)
+    NSC_X3_CASE(3)
+    default:
+      return fail(NSC_E_SHAPE, "fp32 layer with %d output channels", a.cout);
+  }
+#undef NSC_X3_CASE
+  NSC_CHECK_LAUNCH("k_conv_x3");
+  return NSC_OK;
+}
+
+// The first layer: bands of as many tile rows as fit the workgroups per CU,
+// fewer in small calls.  Returns 1 when not even one tile row fits the LDS.
+int launch_first_x3(const CnnLayer& L, ConvArgs a, int32_t max_bt, int64_t max_count,
+                    hipStream_t st) {
+  FirstX3 f{};
+  f.bw = L.w + 3;  // columns -1 .. w + 1 (tap dx = 3 has weight 0)
+  f.inv255 = 1.0 / (double)a.den255;
+  const int nt = L.cout / 16, grp = x3_group(nt);
+  // as many workgroups per CU as the kernel's registers allow; bands of equal height
+  const int32_t per_cu = grp <= 2 ? first_x3_waves<2>() : first_x3_waves<3>();
+  const int32_t row = f.bw * 24;
+  int32_t bt = ((160 * 1024 / per_cu - 1024) / row - 2) / 4;
+  if (bt > a.tiles_y) bt = a.tiles_y;
+  if (max_bt > 0 && bt > max_bt) bt = max_bt;
+  if (bt < 1) bt = 1;
+  const int32_t n_bands = (a.tiles_y + bt - 1) / bt;
+  bt = (a.tiles_y + n_bands - 1) / n_bands;
+  const size_t lds = (size_t)(4 * bt + 2) * row;
+  if (lds > 160 * 1024) return 1;
+  a.band_tiles = bt;
+  const int64_t items = max_count * n_bands * (nt / grp);
+  int64_t grid = (int64_t)kNumCU * per_cu;
+  if (grid > items) grid = items;
+#define NSC_X3_LAUNCH(N, P)                                                                     \
+  if (a.nets)                                                                                   \
+    hipLaunchKernelGGL((k_first_x3<N, P, true>), dim3((unsigned)grid), dim3(256), lds, st, a, f); \
+  else                                                                                          \
+    hipLaunchKernelGGL((k_first_x3<N, P, false>), dim3((unsigned)grid), dim3(256), lds, st, a, f)
+#define NSC_X3_CASE(N)                                                                          \
+  case N:                                                                                       \
+    if (a.pool) {                                                                               \
+      NSC_X3_LAUNCH(N, true);                                                                   \
+    } else {                                                                                    \
+      NSC_X3_LAUNCH(N, false);                                                                  \
+    }                                                                                           \
+    break;
+  switch (grp) {
+    NSC_X3_CASE(1)
+    NSC_X3_CASE(2)
+    NSC_X3_CASE(3)
+    default:
+      return 1;
+  }
+#undef NSC_X3_CASE
+#undef NSC_X3_LAUNCH
+  NSC_CHECK_LAUNCH("k_first_x3");
   return NSC_OK;
 }
 }  // namespace
@@ -2750,6 +3298,25 @@ int run_cnn(const Cnn& cnn, const CnnRunArgs& r, void* ws, size_t ws_bytes, hipS
     const int64_t want = 32 * (int64_t)kNumCU;
     const int64_t min_bands = r.max_count > 0 ? (want + r.max_count - 1) / r.max_count : 1;
     const int32_t max_bt = min_bands <= 1 ? 0 : (int32_t)std::max<int64_t>(1, ty / min_bands);
+    if (!cnn.bf16 && cnn.conv_wx) {  // fp32 layers on the bf16 cores
+      a.wts = static_cast<const unsigned char*>(cnn.conv_wx) + L.wx_off * 2;
+      // two workgroups per CU have work from 512 bands on
+      const int64_t need = (2 * (int64_t)kNumCU + r.max_count - 1) / r.max_count;
+      const int32_t x_bt = need <= 1 ? 0 : (int32_t)std::max<int64_t>(1, ty / need);
+      int rc = 1;
+      if (l == 0) {
+        rc = launch_first_x3(L, a, x_bt, r.max_count, stream);
+      } else {
+        Band64 b{};
+        size_t lds = 0;
+        if (x3_plan(L, x_bt, &b, &a.band_tiles, &lds)) rc = launch_x3(a, b, lds, r.max_count, stream);
+      }
+      if (rc <= 0) {
+        if (rc) return rc;
+        continue;
+      }
+      a = layer_args(l);
+    }
     const size_t lds = conv_lds_bytes(L, cnn.bf16, &a.cin_lds, &a.w_lds, &a.band_w, &a.band_tiles,
                                       &a.seg_tiles, max_bt);
     a.lo_plane = (4 * a.band_tiles + 2) * a.band_w * a.cin_lds;

@@ -225,6 +225,7 @@ struct CnnLayer {
   bool pool;
   int32_t kpad;             // padded reduction length of the packed weights
   size_t w_off, b_off;      // offsets (elements) into the packed weight/bias arrays
+  size_t wx_off;            // fp32 networks: offset (bf16 elements) into conv_wx
   // bf16 networks, fp16 path (layers after the first): the layer's weights
   // enter the fp16 matrix cores multiplied by 2^wexp (exact: every bf16
   // weight within 2^31 of the largest is an fp16 value after the scaling) and
@@ -252,6 +253,9 @@ struct Cnn {
   void* conv_wh;            // bf16 networks: the same as fp16, each layer times 2^wexp
   void* w1h;                // bf16 networks: dense weights as fp16 times 2^dense_wexp
   void* conv_w0h;           // fp16 path: k_pair64's first layer, scaled, bias folded in (or null)
+  void* conv_wx;            // fp32 networks: conv weights as three bf16 parts each, in fragment
+                            // order (first layer: [3 planes of K step 0, 3 pairs of step 1][nt];
+                            // inner layers of 32 k input channels: [channel block][tap][plane][nt])
   void* w1f;                // fp16 path: w1h in fragment order, padded to whole chunks
   int32_t dense_wexp, dense_aexp;  // as CnnLayer::wexp / aexp, for the dense layer
   bool h16;                 // bf16 network whose banded layers and dense layer take the

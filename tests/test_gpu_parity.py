@@ -247,6 +247,24 @@ def test_cnn_fused_pair_shapes(conv, pool, hw, fy):
 
 
 @pytest.mark.parametrize("conv,pool,hw,fy", [
+    ((32, 32), (True, True), (50, 50), 2),            # nested cells, pooled, two tile rows per band
+    ((32, 16), (False, False), (7, 5), 1),            # maps smaller than a tile row
+    ((48, 64), (True, False), (21, 13), 1),           # 48 channels: groups of three; inner fp32 cores
+    ((32, 48, 32), (False, True, False), (23, 31), 1),
+    ((64, 64), (False, True), (25, 50), 1),           # two channel blocks, two output groups
+    ((32, 96, 32), (True, True, False), (18, 22), 1),  # three channel blocks, three output groups
+    ((16, 32, 32), (True, True, False), (17, 120), 1),  # wide: several rounds of tiles per band
+    ((32, 32), (False, False), (5, 230), 1),          # too wide for the bands: fp32 cores
+])
+def test_cnn_fp32_split_shapes(conv, pool, hw, fy):
+    # fp32 layers as three bf16 parts on the bf16 matrix cores, at the edges of
+    # their tiles, bands, channel blocks and output groups
+    spec = synth.CNNSpec(in_h=hw[0], in_w=hw[1], conv=conv, pool=pool, dense=32, bf16=False)
+    _cnn_case(spec, n_frames=16, n_img=9, fy=fy)
+    _cnn_case(spec, n_frames=16, n_img=1, fy=fy, max_count=600)
+
+
+@pytest.mark.parametrize("conv,pool,hw,fy", [
     ((64, 64), (False, True), (13, 9), 1),                 # fused 64-channel pair, ragged tiles
     ((64, 32, 64), (False, False, True), (23, 31), 1),     # fused pair into 32 channels
     ((64, 64, 64), (False, False, False), (7, 5), 1),      # map smaller than a band
