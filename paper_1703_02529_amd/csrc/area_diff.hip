@@ -38,10 +38,18 @@ __device__ __forceinline__ uint32_t bytes13(uint32_t x) {
 // A lane's CB bytes of one row; a 32-byte chunk is two 16-byte halves `split`
 // bytes apart (the halves of all lanes of a strip are two contiguous runs, so
 // that each load instruction of the wave reads consecutive bytes).
-template <int CB>
+// GA: alignment of a 16-byte chunk where it is below 16 (4 or 1; else 0).
+template <int CB, int GA = 0>
 __device__ __forceinline__ void load_chunk(const uint8_t* p, uint32_t (&v)[CB >= 4 ? CB / 4 : 1],
                                            int split = 16) {
-  if constexpr (CB == 32) {
+  if constexpr (CB == 16 && (GA == 4 || GA == 1)) {
+    u32x4 x;
+    __builtin_memcpy(&x, __builtin_assume_aligned(p, GA), 16);
+    v[0] = x[0];
+    v[1] = x[1];
+    v[2] = x[2];
+    v[3] = x[3];
+  } else if constexpr (CB == 32) {
     const u32x4 x = *reinterpret_cast<const u32x4*>(p);
     const u32x4 y = *reinterpret_cast<const u32x4*>(p + split);
     v[0] = x[0];
@@ -113,7 +121,7 @@ struct DiffSums {
 // loads of a batch issued before any add, so that an output row's loads are
 // in flight together (an output row spans 7 to 16 source rows at the frame
 // sizes here).  All control flow is uniform across the wave.
-template <int CB, bool PACKED, int RB = NSC_ROWS_BATCH>
+template <int CB, bool PACKED, int RB = NSC_ROWS_BATCH, int GA = 0>
 __device__ __forceinline__ void vertical_sums(const uint8_t* __restrict__ col, int64_t row_bytes,
                                               int a0, int a1, int q, int j0, int j1,
                                               int32_t out[CB], int split = 16) {
@@ -131,7 +139,7 @@ __device__ __forceinline__ void vertical_sums(const uint8_t* __restrict__ col, i
     uint32_t v[RB][ND];
 #pragma unroll
     for (int k = 0; k < RB; ++k)
-      if (k < cnt) load_chunk<CB>(p + k * row_bytes, v[k], split);
+      if (k < cnt) load_chunk<CB, GA>(p + k * row_bytes, v[k], split);
 #pragma unroll
     for (int k = 0; k < RB; ++k) {
       if (k < cnt) {
@@ -251,25 +259,32 @@ __global__ void __launch_bounds__(1024) k_area_sums_rows(const uint8_t* __restri
 // pieces l and nl + l (col = strip + 16 l).
 // With MAXS > 0 (at most 64 MAXS values per row) the loop over a lane's
 // values is unrolled and cell(k, t, r, s) also gets the slot k (t = l + 64 k).
-template <int CB, bool PACKED, int RB, int MAXS = 0, class Cell, class Buf>
+// GA != 0 (a general strip, CB = 16): the lane's chunk starts lo bytes into
+// the strip, a multiple of GA; chunks may overlap (equal values, written twice).
+template <int CB, bool PACKED, int RB, int MAXS = 0, int GA = 0, class Cell, class Buf>
 __device__ __forceinline__ void strip_band_sums(const uint8_t* __restrict__ col, int64_t row_bytes,
                                                 const Axis& ay, int qx, int Y0, int Y1, int lane,
                                                 int nl, Buf* buf, const int4* xtab, int ncells,
-                                                Cell&& cell) {
+                                                Cell&& cell, int lo = 0) {
   using cell_t = Buf;
   const bool active = lane < nl;
   const int split = 16 * nl;  // CB = 32: bytes from a lane's first piece to its second
   // LDS position (cells) of the lane's c-th 16-byte piece (c = 0, 1 for CB = 32)
-  auto piece = [&](int c) { return CB == 32 ? (c * nl + lane) * 16 : lane * CB; };
+  auto piece = [&](int c) { return GA ? lo : CB == 32 ? (c * nl + lane) * 16 : lane * CB; };
   for (int Y = Y0; Y < Y1; ++Y) {
     // uniform row bounds (divisions run on the vector unit; move them to scalars)
     const int a0 = Y * ay.p, a1 = a0 + ay.p;
     const int j0 = __builtin_amdgcn_readfirstlane(a0 / ay.q);
     const int j1 = __builtin_amdgcn_readfirstlane((a1 + ay.q - 1) / ay.q);
     int32_t v[CB];
-    vertical_sums<CB, PACKED, RB>(col, row_bytes, a0, a1, ay.q, j0, j1, v, split);
+    vertical_sums<CB, PACKED, RB, GA>(col, row_bytes, a0, a1, ay.q, j0, j1, v, split);
     if (active) {
-      if constexpr (PACKED && CB % 8 == 0) {  // 2 CB bytes per lane as 16-byte stores
+      if constexpr (PACKED && GA == 4) {  // 8-byte stores
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<uint2*>(buf + lo + 4 * q) =
+              make_uint2(v[4 * q] | (v[4 * q + 1] << 16), v[4 * q + 2] | (v[4 * q + 3] << 16));
+      } else if constexpr (PACKED && CB % 8 == 0 && GA != 1) {  // 2 CB bytes per lane as 16-byte stores
 #pragma unroll
         for (int q = 0; q < CB / 8; ++q) {
           uint4* d = reinterpret_cast<uint4*>(buf + piece(q / 2)) + (q & 1);
@@ -285,7 +300,7 @@ __device__ __forceinline__ void strip_band_sums(const uint8_t* __restrict__ col,
     auto horizontal = [&](int t) -> int32_t {
       const int x = t / 3, c = t - 3 * x;
       const int4 e = xtab[x];
-      const cell_t* bp = buf + 3 * e.x + c;
+      const cell_t* bp = buf + e.x + c;
       int32_t mid = 0;
       int i = 1;
       for (; i + 8 <= e.y; i += 8) {
@@ -354,13 +369,13 @@ __global__ void __launch_bounds__(256) k_area_sums_wave(const uint8_t* __restric
   const int Ho = ay.n_out, Wo = ax.n_out;
   const int px = ax.p, qx = ax.q;
   const int scols = g.groups_per_wave * g.group_cols;  // output columns of a full strip
-  // per-column table of a strip (identical for every strip): first pixel,
+  // per-column table of a strip (identical for every strip): first byte,
   // pixels after the first, partial weights of the first and last pixel
   int4* xtab = reinterpret_cast<int4*>(smem);
   for (int x = threadIdx.x; x < scols; x += blockDim.x) {
     const int b0 = x * px, b1 = b0 + px;
     const int i0 = b0 / qx, il = (b1 - 1) / qx;
-    xtab[x] = make_int4(i0, il - i0, il == i0 ? px : (i0 + 1) * qx - b0, b1 - il * qx);
+    xtab[x] = make_int4(3 * i0, il - i0, il == i0 ? px : (i0 + 1) * qx - b0, b1 - il * qx);
   }
   __syncthreads();  // the only workgroup barrier
   // each wave's region starts 16-byte aligned (the column sums are stored as uint4)
@@ -413,6 +428,166 @@ __global__ void __launch_bounds__(256) k_area_sums_wave(const uint8_t* __restric
   }
 }
 
+// General strips, for widths whose column pattern splits into no whole groups
+// of lane chunks, or whose rows are not 16-byte aligned: strip s owns the
+// output columns [s cols, (s + 1) cols) and reads the bytes they need, from
+// base(s) on (a multiple of A, the rows' alignment), 16 per lane; the last
+// lane's chunk is moved back to end inside the strip.  Neighbouring strips read
+// a few bytes both.  Against a barrier per output row (k_area_sums_rows):
+// 848x480 -> 50x50 (600 frames) 141 us against 154, frames off 16-byte
+// alignment 141 against 236, 1364x768 -> 100x100 (200 frames) 126 against 232,
+// 301x210 (1,000 frames, one byte per lane before) 57 against 300; against
+// periodic strips of 4 bytes per lane, 500x300 (1,000 frames) 104 against 144.
+// Bands of 4 output rows: of 2, 848x480 -> 100x100 took 205 us, now 181.
+struct GenStrip {
+  int X0, ncols, base, len;  // columns, first byte and bytes (len >= 16)
+};
+__host__ __device__ inline GenStrip gen_strip(const Axis& ax, int cols, int A, int s) {
+  GenStrip g;
+  g.X0 = s * cols;
+  g.ncols = ax.n_out - g.X0 < cols ? ax.n_out - g.X0 : cols;
+  const int row = 3 * ax.n_in;
+  // (out_w <= 2048 columns of p <= 5461 pixels: 32 bits hold the products)
+  g.base = g.X0 * ax.p / ax.q * 3 / A * A;
+  int end = ((g.X0 + g.ncols) * ax.p + ax.q - 1) / ax.q * 3;
+  end = (end + A - 1) / A * A;  // rows are whole multiples of A
+  if (end < g.base + 16) end = g.base + 16 < row ? g.base + 16 : row;
+  if (end - g.base < 16) g.base = end - 16;  // row >= 16; end = row, a multiple of A
+  g.len = end - g.base;
+  return g;
+}
+
+template <bool PACKED, int A>
+__global__ void __launch_bounds__(256) k_area_sums_gen(const uint8_t* __restrict__ frames,
+                                                       int64_t stride, Axis ay, Axis ax,
+                                                       WaveGeom g, int64_t n,
+                                                       int32_t* __restrict__ sums) {
+  using cell_t = typename std::conditional<PACKED, uint16_t, int32_t>::type;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Ho = ay.n_out, Wo = ax.n_out;
+  const int px = ax.p, qx = ax.q;
+  // per-column table of the whole row, first bytes relative to the column's strip
+  int4* xtab = reinterpret_cast<int4*>(smem);
+  for (int x = threadIdx.x; x < Wo; x += blockDim.x) {
+    const int b0 = x * px, b1 = b0 + px;
+    const int i0 = b0 / qx, il = (b1 - 1) / qx;
+    const int rel = 3 * i0 - gen_strip(ax, g.group_cols, A, x / g.group_cols).base;
+    xtab[x] = make_int4(rel, il - i0, il == i0 ? px : (i0 + 1) * qx - b0, b1 - il * qx);
+  }
+  __syncthreads();  // the only workgroup barrier
+  const size_t per_wave = ((size_t)64 * 16 * sizeof(cell_t) +
+                           (size_t)g.band_rows * g.group_cols * 3 * 4 + 15) & ~(size_t)15;
+  unsigned char* wbase = smem + (size_t)Wo * 16 + (size_t)wv * per_wave;
+  cell_t* buf = reinterpret_cast<cell_t*>(wbase);                                  // column sums
+  int32_t* sbuf = reinterpret_cast<int32_t*>(wbase + (size_t)64 * 16 * sizeof(cell_t));  // band sums
+  const int64_t unit = xcd_block(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wv;
+  const int64_t per_frame = (int64_t)g.bands * g.waves_per_frame;
+  if (unit >= n * per_frame) return;
+  const int64_t f = unit / per_frame;
+  const int rem = (int)(unit - f * per_frame);
+  const int band = rem / g.waves_per_frame, strip = rem - band * g.waves_per_frame;
+  const GenStrip gs = gen_strip(ax, g.group_cols, A, strip);
+  const int nl = (gs.len + 15) / 16;  // active lanes, at most 64
+  const int ncells = gs.ncols * 3;
+  const int Y0 = (int)((int64_t)band * Ho / g.bands);
+  const int Y1 = (int)((int64_t)(band + 1) * Ho / g.bands);
+  const int lo = lane < nl ? min(16 * lane, gs.len - 16) : 0;
+  const uint8_t* col = frames + f * stride + gs.base + lo;
+  strip_band_sums<16, PACKED, NSC_ROWS_BATCH, 0, A>(
+      col, (int64_t)ax.n_in * 3, ay, qx, Y0, Y1, lane, nl, buf, xtab + gs.X0, ncells,
+      [&](int t, int r, int32_t s) { sbuf[r * ncells + t] = s; }, lo);
+  int32_t* out = sums + (f * (int64_t)Ho * Wo + gs.X0) * 3;
+  for (int Y = Y0; Y < Y1; ++Y) {
+    const int32_t* srow = sbuf + (Y - Y0) * ncells;
+    int32_t* orow = out + (int64_t)Y * Wo * 3;
+    for (int t = lane; t < ncells; t += 64) orow[t] = srow[t];
+  }
+}
+
+// Small frames: a workgroup copies a whole frame into LDS with contiguous
+// loads and sums each output cell from there, a cell (three channels) per
+// thread and step.  For cells of a few pixels, where rows are too short to
+// fill a wave: 100x100 -> 50x50 21 us against 41 by strips (1,000 frames), 309
+// against 684 (20,000).
+// A: alignment of the frames (16, 4 or 1).
+template <int A>
+__global__ void __launch_bounds__(256) k_area_sums_small(const uint8_t* __restrict__ frames,
+                                                         int64_t stride, Axis ay, Axis ax,
+                                                         int32_t frame_bytes,
+                                                         int32_t* __restrict__ sums) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x;
+  const uint8_t* src = frames + blockIdx.x * stride;
+  if constexpr (A == 1) {
+    for (int i = tid; i < frame_bytes; i += 256) smem[i] = src[i];
+  } else {
+    typedef typename std::conditional<A == 16, uint4, uint32_t>::type V;
+    constexpr int B = 8;  // loads in flight per thread
+    const int nv = frame_bytes / (int)sizeof(V);
+    for (int i0 = tid; i0 < nv; i0 += B * 256) {
+      V v[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (i0 + 256 * b < nv) v[b] = reinterpret_cast<const V*>(src)[i0 + 256 * b];
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (i0 + 256 * b < nv) reinterpret_cast<V*>(smem)[i0 + 256 * b] = v[b];
+    }
+    const int done = nv * (int)sizeof(V);
+    if (tid < frame_bytes - done) smem[done + tid] = src[done + tid];
+  }
+  // per row and column of the grid: first byte offset, pixels after the
+  // first, weights of the first and last pixel (q between them)
+  const int Ho = ay.n_out, Wo = ax.n_out, row_bytes = ax.n_in * 3;
+  int4* tab = reinterpret_cast<int4*>(smem + (frame_bytes + 15) / 16 * 16);
+  for (int i = tid; i < Ho + Wo; i += 256) {
+    const bool row = i < Ho;
+    const int p = row ? ay.p : ax.p, q = row ? ay.q : ax.q;
+    const int b0 = (row ? i : i - Ho) * p, b1 = b0 + p;
+    const int i0 = b0 / q, il = (b1 - 1) / q;
+    tab[i] = make_int4(i0 * (row ? row_bytes : 3), il - i0, il == i0 ? p : (i0 + 1) * q - b0,
+                       b1 - il * q);
+  }
+  __syncthreads();
+  int32_t* out = sums + blockIdx.x * (int64_t)Ho * Wo * 3;
+  const int dY = 256 / Wo, dX = 256 - dY * Wo;
+  int Y = tid / Wo, X = tid - Y * Wo;
+  for (int t = tid; t < Ho * Wo; t += 256) {
+    const int4 ey = tab[Y], ex = tab[Ho + X];
+    const unsigned char* r = smem + ey.x + ex.x;
+    uint32_t s0 = 0, s1 = 0, s2 = 0;
+    for (int j = 0; j <= ey.y; ++j, r += row_bytes) {
+      uint32_t r0 = __umul24(ex.z, r[0]), r1 = __umul24(ex.z, r[1]), r2 = __umul24(ex.z, r[2]);
+      for (int i = 1; i < ex.y; ++i) {
+        r0 += __umul24(ax.q, r[3 * i]);
+        r1 += __umul24(ax.q, r[3 * i + 1]);
+        r2 += __umul24(ax.q, r[3 * i + 2]);
+      }
+      if (ex.y > 0) {
+        r0 += __umul24(ex.w, r[3 * ex.y]);
+        r1 += __umul24(ex.w, r[3 * ex.y + 1]);
+        r2 += __umul24(ex.w, r[3 * ex.y + 2]);
+      }
+      // (frames of at most 48 KB: weights below 2^14, 255 p_x below 2^24)
+      const int wy = j == 0 ? ey.z : j == ey.y ? ey.w : ay.q;
+      s0 += __umul24(wy, r0);
+      s1 += __umul24(wy, r1);
+      s2 += __umul24(wy, r2);
+    }
+    out[3 * t] = (int32_t)s0;
+    out[3 * t + 1] = (int32_t)s1;
+    out[3 * t + 2] = (int32_t)s2;
+    Y += dY;
+    X += dX;
+    if (X >= Wo) {
+      X -= Wo;
+      ++Y;
+    }
+  }
+}
+
 // The earlier-frame global MSE detector fused into the area kernel by
 // temporal tiling along the reuse distance delta: a wave owns one (band,
 // strip) of the R frames f_i = r + delta (sg R + i), i = 0 .. R-1, of chain
@@ -444,7 +619,7 @@ __global__ void __launch_bounds__(256) k_area_prev_wave(const uint8_t* __restric
   for (int x = threadIdx.x; x < scols; x += blockDim.x) {
     const int b0 = x * ax.p, b1 = b0 + ax.p;
     const int i0 = b0 / qx, il = (b1 - 1) / qx;
-    xtab[x] = make_int4(i0, il - i0, il == i0 ? ax.p : (i0 + 1) * qx - b0, b1 - il * qx);
+    xtab[x] = make_int4(3 * i0, il - i0, il == i0 ? ax.p : (i0 + 1) * qx - b0, b1 - il * qx);
   }
   __syncthreads();  // the only workgroup barrier
   const size_t per_wave =
@@ -917,6 +1092,46 @@ int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frame
       p.wave = g.lds_bytes <= 64 * 1024;
     }
   }
+  // Small frames whole in LDS: cells that touch at most 4 pixels (each is read
+  // from LDS byte by byte: at 9 pixels, 120x120 -> 100x100, 122 us against 117
+  // by strips), frames of which three fit a CU, and enough of them for every
+  // CU (128 frames of 100x100: 12 us against 10 by strips).
+  const int cy = p.ay.q == 1 ? p.ay.p : (p.ay.p - 1) / p.ay.q + 2;
+  const int cx = p.ax.q == 1 ? p.ax.p : (p.ax.p - 1) / p.ax.q + 2;
+  p.small = row_bytes * in_h <= 48 * 1024 && cy * cx <= 4 && n >= kNumCU;
+  p.align = p.chunk_bytes;
+  // general strips, where the periodic ones do not apply or read 4 bytes per lane
+  p.gen = false;
+  if (!p.small && (!p.wave || p.wg.chunk_bytes == 4) && row_bytes >= 16 && out_w <= 2048) {
+    WaveGeom g{};
+    for (int32_t strips = (int32_t)((row_bytes + 1023) / 1024); strips <= out_w; ++strips) {
+      const int32_t cols = (out_w + strips - 1) / strips;
+      bool fits = true;
+      for (int32_t s = 0; s * cols < out_w && fits; ++s)
+        fits = gen_strip(p.ax, cols, p.align, s).len <= 1024;
+      if (!fits) continue;
+      g.group_cols = cols;
+      g.waves_per_frame = (out_w + cols - 1) / cols;
+      break;
+    }
+    if (g.group_cols > 0) {
+      g.chunk_bytes = 16;
+      g.waves_per_block = g.waves_per_frame <= 4 ? g.waves_per_frame * (4 / g.waves_per_frame) : 4;
+      // bands of four output rows (the column table of the whole row is set up
+      // once per band), more when there are too few frames
+      int64_t wb = (out_h + 4 - 1) / 4;
+      const int64_t fill = (16384 + n * g.waves_per_frame - 1) / (n * g.waves_per_frame > 0 ? n * g.waves_per_frame : 1);
+      if (fill > wb) wb = fill;
+      if (wb > out_h) wb = out_h;
+      g.bands = (int32_t)wb;
+      g.band_rows = (int32_t)((out_h + wb - 1) / wb);
+      const int64_t per_wave =
+          (64 * 16 * (p.packed ? 2 : 4) + (int64_t)g.band_rows * g.group_cols * 3 * 4 + 15) & ~(int64_t)15;
+      g.lds_bytes = (size_t)(out_w * 16 + g.waves_per_block * per_wave);
+      p.gen = g.lds_bytes <= 64 * 1024;
+      p.gg = g;
+    }
+  }
   // split frames into bands of output rows when there are too few frames to fill the chip
   int64_t bands = (4096 + n - 1) / (n > 0 ? n : 1);
   if (bands < 1) bands = 1;
@@ -933,6 +1148,41 @@ int launch_area_sums(const AreaPlan& p, const uint8_t* frames, int64_t stride, i
   if (blocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
   const size_t row_bytes = (size_t)p.ax.n_in * 3;
   dim3 grid((unsigned)blocks), block(p.threads);
+  if (p.small) {
+    const int32_t bytes = (int32_t)(row_bytes * p.ay.n_in);
+    const size_t lds = (size_t)(bytes + 15) / 16 * 16 + (size_t)(p.ay.n_out + p.ax.n_out) * 16;
+#define NSC_SMALL_LAUNCH(A)                                                                      \
+  hipLaunchKernelGGL(k_area_sums_small<A>, dim3((unsigned)n), dim3(256), lds, \
+                     stream, frames, stride, p.ay, p.ax, bytes, sums)
+    if (p.align == 16)
+      NSC_SMALL_LAUNCH(16);
+    else if (p.align == 4)
+      NSC_SMALL_LAUNCH(4);
+    else
+      NSC_SMALL_LAUNCH(1);
+#undef NSC_SMALL_LAUNCH
+    NSC_CHECK_LAUNCH("k_area_sums_small");
+    return NSC_OK;
+  }
+  if (p.gen) {
+    const WaveGeom& g = p.gg;
+    const int64_t units = n * g.bands * g.waves_per_frame;
+    const int64_t wblocks = (units + g.waves_per_block - 1) / g.waves_per_block;
+    if (wblocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
+#define NSC_GEN_LAUNCH(PK, A)                                                                    \
+  hipLaunchKernelGGL((k_area_sums_gen<PK, A>), dim3((unsigned)wblocks), dim3(64 * g.waves_per_block), \
+                     g.lds_bytes, stream, frames, stride, p.ay, p.ax, g, n, sums)
+    if (p.align == 16) {
+      if (p.packed) NSC_GEN_LAUNCH(true, 16); else NSC_GEN_LAUNCH(false, 16);
+    } else if (p.align == 4) {
+      if (p.packed) NSC_GEN_LAUNCH(true, 4); else NSC_GEN_LAUNCH(false, 4);
+    } else {
+      if (p.packed) NSC_GEN_LAUNCH(true, 1); else NSC_GEN_LAUNCH(false, 1);
+    }
+#undef NSC_GEN_LAUNCH
+    NSC_CHECK_LAUNCH("k_area_sums_gen");
+    return NSC_OK;
+  }
   if (p.wave) {
     const WaveGeom& g = p.wg;
     const int64_t units = n * g.bands * g.waves_per_frame;
@@ -1085,7 +1335,7 @@ void area_prev_diff_args(const PrevFusePlan& fp, const int64_t* part, DiffArgs* 
 }
 
 bool area_detect_fused(const AreaPlan& p, const DiffArgs& a) {
-  return p.wave && a.ref_mode == NSC_REF_FIXED && a.grid_h * a.grid_w == 1 && a.cams == nullptr &&
+  return p.wave && !p.small && a.ref_mode == NSC_REF_FIXED && a.grid_h * a.grid_w == 1 && a.cams == nullptr &&
          a.metric >= NSC_METRIC_MSE && a.metric <= NSC_METRIC_PSNR;
 }
 

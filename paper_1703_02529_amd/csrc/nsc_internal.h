@@ -83,6 +83,10 @@ struct AreaPlan {
   bool packed;           // 16-bit packed vertical accumulators are exact
   bool wave;             // wave-autonomous strips apply (else the per-row kernel)
   WaveGeom wg;
+  int32_t align;         // alignment of the rows: 16, 4 or 1
+  bool small;            // a whole frame in LDS (k_area_sums_small) for the plain sums
+  bool gen;              // general strips (k_area_sums_gen) for the plain sums
+  WaveGeom gg;           // their geometry: group_cols columns per strip
 };
 int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frames,
                    int32_t out_h, int32_t out_w, int64_t n, AreaPlan* plan);

@@ -85,6 +85,35 @@ def test_downsample_parity(H, W, Ho, Wo, pad):
         assert np.array_equal(got[f], ref), f"frame {f}"
 
 
+@pytest.mark.parametrize("H,W,Ho,Wo,pad,shift,n", [
+    (100, 100, 50, 50, 0, 0, 256),    # whole frames in LDS: 16-byte frames,
+    (100, 101, 100, 101, 0, 1, 260),  # ... any alignment, a tail of bytes
+    (50, 100, 25, 50, 4, 4, 300),     # ... 4-byte frames
+    (100, 100, 50, 50, 0, 0, 3),      # too few for that: general strips, last chunk moved back
+    (96, 848, 50, 50, 0, 0, 4),       # three general strips of 16-byte rows
+    (96, 848, 50, 100, 12, 4, 4),     # ... of 4-byte rows, padded
+    (40, 341, 7, 50, 5, 3, 3),        # ... at any alignment
+    (31, 6, 3, 5, 0, 0, 3),           # rows of 18 bytes: two chunks that overlap
+    (31, 5, 3, 5, 1, 0, 3),           # rows of 15 bytes: below one chunk
+    (700, 340, 2, 17, 0, 0, 3),       # 350 source rows per output row: unpacked general strips
+    (20, 1364, 20, 1364, 0, 0, 2),    # identity of a wide 4-byte row
+])
+def test_downsample_general_strips(H, W, Ho, Wo, pad, shift, n):
+    """Frames at the end of their allocation, at every alignment, on the forms
+    for general widths and small frames."""
+    fb = H * W * 3
+    stride = fb + pad
+    host = rng.integers(0, 256, size=(n - 1) * stride + fb, dtype=np.uint8)
+    dev = torch.empty(shift + host.size, dtype=torch.uint8, device=DEV)[shift:]
+    dev.copy_(torch.from_numpy(host))
+    out = torch.empty(n * Ho * Wo * 3, dtype=torch.int32, device=DEV)
+    nsc.nsc_downsample(dev, n, H, W, Ho, Wo, out, frame_stride=stride)
+    got = out.cpu().numpy().reshape(n, Ho, Wo, 3)
+    for f in sorted({0, 1, n // 2, n - 1}):
+        ref = oracle.area_sums(host[f * stride:f * stride + fb].reshape(H, W, 3), Ho, Wo)
+        assert np.array_equal(got[f], ref), f"frame {f}"
+
+
 def test_downsample_extremes():
     # all-255 frames reach the largest sums; all-0 frames give zeros
     H, W = 720, 1280
