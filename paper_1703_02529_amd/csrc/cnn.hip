@@ -2105,6 +2105,159 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// First layer of a bf16 network that is fused with no second one (as the
+// pooling 64-channel one): the pre-processed bf16 input band in LDS, 8 bytes
+// per pixel, tiles and stores as in k_first_x3, two MFMAs per tile and 16
+// channels.  Stores fp32, or fp16 times the next layer's input scale.  Bound
+// by the gather of the area sums and its latency.  1,501 images of 100x100
+// sums, 64 channels: FBNEW us against 125 with the weights in LDS and a
+// 2-byte store per value (k_conv_first).
+template <int NT, bool POOL, bool G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+    k_first_bf16(ConvArgs a, int32_t bw) {
+  using X = Elt<uint16_t>;
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  int64_t cnt = *a.count;
+  if (cnt > a.max_count) cnt = a.max_count;
+  const int bands = (a.tiles_y + a.band_tiles - 1) / a.band_tiles;
+  const int ntw = a.cout / 16, ngrp = ntw / NT;
+  const int64_t items = cnt * bands * ngrp;
+  constexpr uint32_t kPix = 8;
+  constexpr int R = POOL ? 2 : 1;          // pixels per unit (window or pixel) and axis
+  constexpr int UPT = POOL ? 4 : 16;       // units per tile
+  constexpr int ADV = UPT * kBandWaves;    // units from one tile of a wave to its next
+  const int wo = a.w / R, ho = a.h / R;
+  const int hn = ho * R;
+  const int adv_r = ADV / wo, adv_x = ADV - adv_r * wo;
+  const uint32_t q_adv = (uint32_t)(R * (adv_r * bw + adv_x)) * kPix;
+  const uint32_t q_wrap = (uint32_t)(R * (bw - wo)) * kPix;
+  // K chunks (dy, dx) = (g / 2, 2 (g mod 2)) and (2, 2 (g mod 2)); the latter
+  // has zero weights for lane groups 2 and 3
+  const uint32_t o0 = (uint32_t)((g >> 1) * bw + 2 * (g & 1)) * kPix;
+  const uint32_t o1 = (uint32_t)(2 * bw + 2 * (g & 1)) * kPix;
+  const uint32_t eight = (uint32_t)opaque(8);
+  const uint32_t o0b = o0 + eight, o1b = o1 + eight;
+  const int j = POOL ? m & 3 : 0;          // pixel of the window
+  const int u_lane = wave * UPT + (POOL ? m >> 2 : m);
+  const int ur0 = band_row(u_lane, 1.0f / (float)wo), ux0 = u_lane - ur0 * wo;
+  const uint32_t q0 = (uint32_t)((R * ur0 + (j >> 1)) * bw + R * ux0 + (j & 1)) * kPix;
+  auto ld = [&](uint32_t lo, uint32_t hi) {
+    const uint2 p = *reinterpret_cast<const uint2*>(lds + lo);
+    const uint2 q = *reinterpret_cast<const uint2*>(lds + hi);
+    return __builtin_bit_cast(bf16x8, make_uint4(p.x, p.y, q.x, q.y));
+  };
+  bf16x8 w[2][NT];
+  f32x4 bias[NT];
+  int64_t w_off = 0;
+  int w_grp = -1;
+  float st16 = 0.0f;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t s = item / (bands * ngrp);
+    const int bg = (int)(item - s * (bands * ngrp));
+    const int bi = bg / ngrp, grp = bg - bi * ngrp;
+    const int ty0 = bi * a.band_tiles;
+    const int nty = min(a.band_tiles, a.tiles_y - ty0);
+    const int rows = min(4 * nty, hn - 4 * ty0);
+    const int64_t off = G ? slot_woff(a.nets, a.per_cam, a.idx, s) : 0;  // camera group
+    if (off != w_off || grp != w_grp) {  // uniform: once without groups
+      const bf16x8* wf = at_off(reinterpret_cast<const bf16x8*>(a.wts), off) + grp * NT * 64 + lane;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) w[q][nt] = wf[(q * ntw + nt) * 64];
+      const float* bp = at_off(a.bias, off) + grp * NT * 16 + 4 * g;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(bp + nt * 16);
+      if (a.out_f16) st16 = at_off(a.scl, off)[2];
+      w_off = off;
+      w_grp = grp;
+    }
+    __syncthreads();  // the previous item's readers are done
+    {
+      const int npix = (4 * nty + 2) * bw;
+      const float inv_bw = 1.0f / (float)bw;
+#pragma unroll 4
+      for (int p = threadIdx.x; p < npix; p += 256) {
+        const int br = band_row(p, inv_bw), bc = p - br * bw;
+        const int y = 4 * ty0 - 1 + br, x = bc - 1;
+        uint2 v = make_uint2(0u, 0u);
+        if ((unsigned)y < (unsigned)a.h && (unsigned)x < (unsigned)a.w) {
+          v = first_input_bf16(a, s, y, x);
+          v.y &= 0xFFFFu;  // channel 3 is 0 here
+        }
+        *reinterpret_cast<uint2*>(lds + p * kPix) = v;
+      }
+    }
+    __syncthreads();
+    const int units = rows / R * wo;  // of the band
+    const int ntile = (units + UPT - 1) / UPT;
+    int u = u_lane, ux = ux0;
+    uint32_t qn = q0;
+    // units are the band's outputs in raster order, so they follow one another in memory
+    int64_t e = (s * (int64_t)ho + 4 / R * ty0) * wo * a.cout + grp * NT * 16 + 4 * g +
+                u_lane * a.cout + (POOL ? 16 * j : 0);
+    for (int t = wave; t < ntile; t += kBandWaves) {
+      const bool in = u < units;
+      const uint32_t q = in ? qn : 0u;
+      const bf16x8 x0 = ld(q + o0, q + o0b), x1 = ld(q + o1, q + o1b);
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], x0, bias[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[1][nt], x1, acc[nt]);
+      // ReLU and pooling on the bits, as in k_first_x3
+      int4 r[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        int v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          v[k] = __float_as_int(acc[nt][k]);
+          if constexpr (POOL) {
+            v[k] = max(v[k], __builtin_amdgcn_update_dpp(0, v[k], kQuadXor1, 0xF, 0xF, true));
+            v[k] = max(v[k], __builtin_amdgcn_update_dpp(0, v[k], kQuadXor2, 0xF, 0xF, true));
+          }
+          v[k] = max(v[k], 0);
+        }
+        r[nt] = make_int4(v[0], v[1], v[2], v[3]);
+      }
+      auto store = [&](int64_t at, const int4& v) {
+        if (a.out_f16)
+          *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(a.act_out) + at) =
+              f16x4_bits(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z),
+                         __int_as_float(v.w), st16);
+        else
+          *reinterpret_cast<int4*>(a.act_out + at) = v;
+      };
+      if constexpr (POOL) {  // the window's lane j stores output block j
+        int4 q4 = r[0];
+#pragma unroll
+        for (int nt = 1; nt < NT; ++nt) {
+          q4.x = j == nt ? r[nt].x : q4.x;
+          q4.y = j == nt ? r[nt].y : q4.y;
+          q4.z = j == nt ? r[nt].z : q4.z;
+          q4.w = j == nt ? r[nt].w : q4.w;
+        }
+        if (in && j < NT) store(e, q4);
+      } else if (in) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) store(e + nt * 16, r[nt]);
+      }
+      u += ADV;
+      e += ADV * a.cout;
+      ux += adv_x;
+      qn += q_adv;
+      if (ux >= wo) {
+        ux -= wo;
+        qn += q_wrap;
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ dense
 
 struct DenseArgs {
@@ -3118,6 +3271,51 @@ int launch_first_x3(const CnnLayer& L, ConvArgs a, int32_t max_bt, int64_t max_c
   NSC_CHECK_LAUNCH("k_first_x3");
   return NSC_OK;
 }
+// The same for a bf16 network's first layer (k_first_bf16).
+int launch_first_bf16(const CnnLayer& L, ConvArgs a, int32_t max_bt, int64_t max_count,
+                      hipStream_t st) {
+  const int nt = L.cout / 16, grp = nt <= 4 ? nt : (nt == 6 ? 3 : 4);
+  const int32_t bw = L.w + 3;  // columns -1 .. w + 1 (tap dx = 3 has weight 0)
+  const int32_t per_cu = 4;    // workgroups per CU, by the kernel's registers
+  const int32_t row = bw * 8;
+  int32_t bt = ((160 * 1024 / per_cu - 1024) / row - 2) / 4;
+  if (bt > a.tiles_y) bt = a.tiles_y;
+  if (max_bt > 0 && bt > max_bt) bt = max_bt;
+  if (bt < 1) bt = 1;
+  const int32_t n_bands = (a.tiles_y + bt - 1) / bt;
+  bt = (a.tiles_y + n_bands - 1) / n_bands;
+  const size_t lds = (size_t)(4 * bt + 2) * row;
+  if (lds > 160 * 1024) return 1;
+  a.band_tiles = bt;
+  const int64_t items = max_count * n_bands * (nt / grp);
+  int64_t grid = (int64_t)kNumCU * per_cu;
+  if (grid > items) grid = items;
+#define NSC_FB_LAUNCH(N, P)                                                                     \
+  if (a.nets)                                                                                   \
+    hipLaunchKernelGGL((k_first_bf16<N, P, true>), dim3((unsigned)grid), dim3(256), lds, st, a, bw); \
+  else                                                                                          \
+    hipLaunchKernelGGL((k_first_bf16<N, P, false>), dim3((unsigned)grid), dim3(256), lds, st, a, bw)
+#define NSC_FB_CASE(N)                                                                          \
+  case N:                                                                                       \
+    if (a.pool) {                                                                               \
+      NSC_FB_LAUNCH(N, true);                                                                   \
+    } else {                                                                                    \
+      NSC_FB_LAUNCH(N, false);                                                                  \
+    }                                                                                           \
+    break;
+  switch (grp) {
+    NSC_FB_CASE(1)
+    NSC_FB_CASE(2)
+    NSC_FB_CASE(3)
+    NSC_FB_CASE(4)
+    default:
+      return 1;
+  }
+#undef NSC_FB_CASE
+#undef NSC_FB_LAUNCH
+  NSC_CHECK_LAUNCH("k_first_bf16");
+  return NSC_OK;
+}
 }  // namespace
 
 // Two ping-pong buffers of fp32 activations per image, then (fused 64-channel
@@ -3298,6 +3496,16 @@ int run_cnn(const Cnn& cnn, const CnnRunArgs& r, void* ws, size_t ws_bytes, hipS
     const int64_t want = 32 * (int64_t)kNumCU;
     const int64_t min_bands = r.max_count > 0 ? (want + r.max_count - 1) / r.max_count : 1;
     const int32_t max_bt = min_bands <= 1 ? 0 : (int32_t)std::max<int64_t>(1, ty / min_bands);
+    if (cnn.bf16 && l == 0) {
+      // four workgroups per CU have work from 1,024 bands on
+      const int64_t need = (4 * (int64_t)kNumCU + r.max_count - 1) / r.max_count;
+      const int32_t x_bt = need <= 1 ? 0 : (int32_t)std::max<int64_t>(1, ty / need);
+      ConvArgs f = a;
+      f.wts = frag_weights(0, false);
+      const int rc = launch_first_bf16(L, f, x_bt, r.max_count, stream);
+      if (rc < 0) return rc;
+      if (rc == 0) continue;
+    }
     if (!cnn.bf16 && cnn.conv_wx) {  // fp32 layers on the bf16 cores
       a.wts = static_cast<const unsigned char*>(cnn.conv_wx) + L.wx_off * 2;
       // two workgroups per CU have work from 512 bands on
