@@ -1098,7 +1098,9 @@ int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frame
   // CU (128 frames of 100x100: 12 us against 10 by strips).
   const int cy = p.ay.q == 1 ? p.ay.p : (p.ay.p - 1) / p.ay.q + 2;
   const int cx = p.ax.q == 1 ? p.ax.p : (p.ax.p - 1) / p.ax.q + 2;
-  p.small = row_bytes * in_h <= 48 * 1024 && cy * cx <= 4 && n >= kNumCU;
+  // (rows and columns of the grid take 16 bytes each of LDS: a column of
+  // 1x8192 pixels kept at its size would need more than a CU has)
+  p.small = row_bytes * in_h + 16LL * (out_h + out_w) <= 52 * 1024 && cy * cx <= 4 && n >= kNumCU;
   p.align = p.chunk_bytes;
   // general strips, where the periodic ones do not apply or read 4 bytes per lane
   p.gen = false;

@@ -2110,7 +2110,7 @@ __global__ void __launch_bounds__(256)
 // per pixel, tiles and stores as in k_first_x3, two MFMAs per tile and 16
 // channels.  Stores fp32, or fp16 times the next layer's input scale.  Bound
 // by the gather of the area sums and its latency.  1,501 images of 100x100
-// sums, 64 channels: FBNEW us against 125 with the weights in LDS and a
+// sums, 64 channels: 104 us against 125 with the weights in LDS and a
 // 2-byte store per value (k_conv_first).
 template <int NT, bool POOL, bool G>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))

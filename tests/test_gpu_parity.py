@@ -97,6 +97,7 @@ def test_downsample_parity(H, W, Ho, Wo, pad):
     (31, 5, 3, 5, 1, 0, 3),           # rows of 15 bytes: below one chunk
     (700, 340, 2, 17, 0, 0, 3),       # 350 source rows per output row: unpacked general strips
     (20, 1364, 20, 1364, 0, 0, 2),    # identity of a wide 4-byte row
+    (12000, 1, 12000, 1, 0, 0, 256),  # a frame that fits LDS, its table of rows does not
 ])
 def test_downsample_general_strips(H, W, Ho, Wo, pad, shift, n):
     """Frames at the end of their allocation, at every alignment, on the forms
@@ -291,6 +292,23 @@ def test_cnn_fp32_split_shapes(conv, pool, hw, fy):
     spec = synth.CNNSpec(in_h=hw[0], in_w=hw[1], conv=conv, pool=pool, dense=32, bf16=False)
     _cnn_case(spec, n_frames=16, n_img=9, fy=fy)
     _cnn_case(spec, n_frames=16, n_img=1, fy=fy, max_count=600)
+
+
+@pytest.mark.parametrize("conv,pool,hw,fy", [
+    ((64, 64), (True, True), (50, 50), 2),    # pooled 64 channels, nested cells: fp16 into a band
+    ((16,), (True,), (7, 5), 1),              # one store lane of four, a last pooled row cut off
+    ((32,), (False,), (4, 16), 1),            # one band whose pixels are whole tiles
+    ((48,), (True,), (21, 13), 1),            # three blocks, ragged windows
+    ((96,), (False,), (9, 18), 1),            # two groups of three blocks
+    ((128,), (True,), (18, 3), 1),            # two groups of four, one window per row
+    ((16,), (False,), (6, 400), 1),           # rows of several rounds of tiles
+])
+def test_cnn_first_layer_alone_shapes(conv, pool, hw, fy):
+    # a bf16 network's first layer fused with no second one, at the edges of its
+    # tiles, bands and output groups; few and many bands per image
+    spec = synth.CNNSpec(in_h=hw[0], in_w=hw[1], conv=conv, pool=pool, dense=32, bf16=True)
+    _cnn_case(spec, n_frames=16, n_img=9, fy=fy)
+    _cnn_case(spec, n_frames=16, n_img=1, fy=fy, max_count=2000)
 
 
 @pytest.mark.parametrize("conv,pool,hw,fy", [
