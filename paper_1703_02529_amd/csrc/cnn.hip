@@ -1701,7 +1701,8 @@ k_pair64(ConvArgs a0, ConvArgs a1, Band64 b, const uint2* __restrict__ xin, int3
 // Weights are split on the host, in fragment order.
 
 // The three bf16 parts of 8 fp32 values, packed (0 remainders for infinities
-// and NaN, so that these pass through as in one product).
+// and NaN; a sum that an infinite value reaches is infinite or, where a part of
+// its weight is zero, NaN).
 __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& h, uint4& m,
                                        uint4& l) {
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
