@@ -433,16 +433,20 @@ __global__ void __launch_bounds__(256) k_area_sums_wave(const uint8_t* __restric
 // output columns [s cols, (s + 1) cols) and reads the bytes they need, from
 // base(s) on (a multiple of A, the rows' alignment), 16 per lane; the last
 // lane's chunk is moved back to end inside the strip.  Neighbouring strips read
-// a few bytes both.  Against a barrier per output row (k_area_sums_rows):
-// 848x480 -> 50x50 (600 frames) 141 us against 154, frames off 16-byte
-// alignment 141 against 236, 1364x768 -> 100x100 (200 frames) 126 against 232,
-// 301x210 (1,000 frames, one byte per lane before) 57 against 300; against
-// periodic strips of 4 bytes per lane, 500x300 (1,000 frames) 104 against 144.
-// Bands of 4 output rows: of 2, 848x480 -> 100x100 took 205 us, now 181.
+// a few bytes both.  A wave sets up its own strip's columns, without a barrier;
+// the strips' bytes come from the host (the whole row's columns per workgroup,
+// with 64-bit divisions: 0.7 us more for one frame, and 848x480 -> 100x100 34.1
+// us for 100 frames against 27.4).  Against a barrier per output
+// row (k_area_sums_rows): 848x480 -> 50x50 (600 frames) 143 us against 152,
+// frames off 16-byte alignment 110 against 150 (640x480), 1364x768 -> 100x100
+// (200 frames) 124 against 232, 301x210 (600 frames, one byte per lane before)
+// 28.6 against 193; against periodic strips of 4 bytes per lane, 500x300 (600
+// frames) 47 against 85.  Bands of 4 output rows: of 2, 848x480 -> 100x100
+// took 17 % longer.
 struct GenStrip {
   int X0, ncols, base, len;  // columns, first byte and bytes (len >= 16)
 };
-__host__ __device__ inline GenStrip gen_strip(const Axis& ax, int cols, int A, int s) {
+inline GenStrip gen_strip(const Axis& ax, int cols, int A, int s) {
   GenStrip g;
   g.X0 = s * cols;
   g.ncols = ax.n_out - g.X0 < cols ? ax.n_out - g.X0 : cols;
@@ -457,10 +461,16 @@ __host__ __device__ inline GenStrip gen_strip(const Axis& ax, int cols, int A, i
   return g;
 }
 
+// LDS bytes of one wave of k_area_sums_gen.
+__host__ __device__ inline size_t gen_wave_lds(bool packed, int band_rows, int cols) {
+  return ((size_t)64 * 16 * (packed ? 2 : 4) + (size_t)cols * 16 +
+          (size_t)band_rows * cols * 3 * 4 + 15) & ~(size_t)15;
+}
+
 template <bool PACKED, int A>
 __global__ void __launch_bounds__(256) k_area_sums_gen(const uint8_t* __restrict__ frames,
                                                        int64_t stride, Axis ay, Axis ax,
-                                                       WaveGeom g, int64_t n,
+                                                       WaveGeom g, GenStrips strips, int64_t n,
                                                        int32_t* __restrict__ sums) {
   using cell_t = typename std::conditional<PACKED, uint16_t, int32_t>::type;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -468,37 +478,38 @@ __global__ void __launch_bounds__(256) k_area_sums_gen(const uint8_t* __restrict
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int Ho = ay.n_out, Wo = ax.n_out;
   const int px = ax.p, qx = ax.q;
-  // per-column table of the whole row, first bytes relative to the column's strip
-  int4* xtab = reinterpret_cast<int4*>(smem);
-  for (int x = threadIdx.x; x < Wo; x += blockDim.x) {
-    const int b0 = x * px, b1 = b0 + px;
-    const int i0 = b0 / qx, il = (b1 - 1) / qx;
-    const int rel = 3 * i0 - gen_strip(ax, g.group_cols, A, x / g.group_cols).base;
-    xtab[x] = make_int4(rel, il - i0, il == i0 ? px : (i0 + 1) * qx - b0, b1 - il * qx);
-  }
-  __syncthreads();  // the only workgroup barrier
-  const size_t per_wave = ((size_t)64 * 16 * sizeof(cell_t) +
-                           (size_t)g.band_rows * g.group_cols * 3 * 4 + 15) & ~(size_t)15;
-  unsigned char* wbase = smem + (size_t)Wo * 16 + (size_t)wv * per_wave;
-  cell_t* buf = reinterpret_cast<cell_t*>(wbase);                                  // column sums
-  int32_t* sbuf = reinterpret_cast<int32_t*>(wbase + (size_t)64 * 16 * sizeof(cell_t));  // band sums
   const int64_t unit = xcd_block(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wv;
-  const int64_t per_frame = (int64_t)g.bands * g.waves_per_frame;
-  if (unit >= n * per_frame) return;
-  const int64_t f = unit / per_frame;
+  const int per_frame = g.bands * g.waves_per_frame;
+  const int64_t units = n * per_frame;
+  if (unit >= units) return;  // no workgroup barrier follows
+  // (a 64-bit division takes about as long as the band's loads)
+  const int64_t f = units <= UINT32_MAX ? (int64_t)((uint32_t)unit / (uint32_t)per_frame)
+                                        : unit / per_frame;
   const int rem = (int)(unit - f * per_frame);
   const int band = rem / g.waves_per_frame, strip = rem - band * g.waves_per_frame;
-  const GenStrip gs = gen_strip(ax, g.group_cols, A, strip);
-  const int nl = (gs.len + 15) / 16;  // active lanes, at most 64
-  const int ncells = gs.ncols * 3;
-  const int Y0 = (int)((int64_t)band * Ho / g.bands);
-  const int Y1 = (int)((int64_t)(band + 1) * Ho / g.bands);
-  const int lo = lane < nl ? min(16 * lane, gs.len - 16) : 0;
-  const uint8_t* col = frames + f * stride + gs.base + lo;
+  const int base = (int)(strips.at[strip] & 0xFFFFu), len = (int)(strips.at[strip] >> 16);
+  const int X0 = strip * g.group_cols;
+  const int ncols = min(g.group_cols, Wo - X0), ncells = 3 * ncols;
+  const int nl = (len + 15) / 16;  // active lanes, at most 64
+  const int Y0 = band * g.band_rows, Y1 = min(Ho, Y0 + g.band_rows);
+  // the wave's LDS: column sums, the strip's column table (first byte, pixels
+  // after the first, weights of the first and last pixel), the band's sums
+  unsigned char* wbase = smem + (size_t)wv * gen_wave_lds(PACKED, g.band_rows, g.group_cols);
+  cell_t* buf = reinterpret_cast<cell_t*>(wbase);
+  int4* xtab = reinterpret_cast<int4*>(wbase + (size_t)64 * 16 * sizeof(cell_t));
+  int32_t* sbuf = reinterpret_cast<int32_t*>(xtab + g.group_cols);
+  for (int x = lane; x < ncols; x += 64) {
+    const int b0 = (X0 + x) * px, b1 = b0 + px;
+    const int i0 = b0 / qx, il = (b1 - 1) / qx;
+    xtab[x] = make_int4(3 * i0 - base, il - i0, il == i0 ? px : (i0 + 1) * qx - b0, b1 - il * qx);
+  }
+  // (the __syncwarp before the first horizontal pass orders the table's reads too)
+  const int lo = lane < nl ? min(16 * lane, len - 16) : 0;
+  const uint8_t* col = frames + f * stride + base + lo;
   strip_band_sums<16, PACKED, NSC_ROWS_BATCH, 0, A>(
-      col, (int64_t)ax.n_in * 3, ay, qx, Y0, Y1, lane, nl, buf, xtab + gs.X0, ncells,
+      col, (int64_t)ax.n_in * 3, ay, qx, Y0, Y1, lane, nl, buf, xtab, ncells,
       [&](int t, int r, int32_t s) { sbuf[r * ncells + t] = s; }, lo);
-  int32_t* out = sums + (f * (int64_t)Ho * Wo + gs.X0) * 3;
+  int32_t* out = sums + (f * (int64_t)Ho * Wo + X0) * 3;
   for (int Y = Y0; Y < Y1; ++Y) {
     const int32_t* srow = sbuf + (Y - Y0) * ncells;
     int32_t* orow = out + (int64_t)Y * Wo * 3;
@@ -570,7 +581,7 @@ __global__ void __launch_bounds__(256) k_area_sums_small(const uint8_t* __restri
         r1 += __umul24(ex.w, r[3 * ex.y + 1]);
         r2 += __umul24(ex.w, r[3 * ex.y + 2]);
       }
-      // (frames of at most 48 KB: weights below 2^14, 255 p_x below 2^24)
+      // (frames of at most 52 KB: weights below 2^15, 255 p_x below 2^24)
       const int wy = j == 0 ? ey.z : j == ey.y ? ey.w : ay.q;
       s0 += __umul24(wy, r0);
       s1 += __umul24(wy, r1);
@@ -1102,15 +1113,31 @@ int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frame
   // 1x8192 pixels kept at its size would need more than a CU has)
   p.small = row_bytes * in_h + 16LL * (out_h + out_w) <= 52 * 1024 && cy * cx <= 4 && n >= kNumCU;
   p.align = p.chunk_bytes;
-  // general strips, where the periodic ones do not apply or read 4 bytes per lane
+  // General strips, where the periodic ones do not apply or read 4 bytes per
+  // lane.  Calls of few output rows (in waves of the kernel with a barrier per
+  // row) stay with the other form, whose waves start with less work.  That
+  // kernel with 16 bytes per lane, whose loads are as wide, is behind only where
+  // the chip is full several times over: 848x480 -> 100x100, 40 frames 13.1 us
+  // against 14.7, 80 frames 21.7 against 23.2, 200 frames 49.5 against 48.3, 600
+  // frames 192 against 162; -> 50x50, 16 frames 4.9 against 5.3, 60 frames on
+  // fresh buffers 15.8 against 16.6, 200 frames 41.9 against 39.5.  With 4 or 1
+  // bytes per lane it is behind from a few frames on: 640x480 off alignment, 4
+  // frames 4.4 against 4.7, 8 frames 5.5 against 4.7; 301x210, 4 frames 4.0
+  // against 4.7, 8 frames 6.3 against 4.8.  Periodic strips of 4 bytes per lane:
+  // 200x200 -> 100x100, one frame 4.0 against 4.3, 6 frames 4.5 against 4.4.
+  const int64_t row_waves = n * out_h * (p.threads / 64);
+  const bool few = row_waves < (p.wave ? 1000 : p.chunk_bytes == 16 ? 30000 : 3100);
   p.gen = false;
-  if (!p.small && (!p.wave || p.wg.chunk_bytes == 4) && row_bytes >= 16 && out_w <= 2048) {
+  if (!p.small && !few && (!p.wave || p.wg.chunk_bytes == 4) && row_bytes >= 16 && out_w <= 2048) {
     WaveGeom g{};
     for (int32_t strips = (int32_t)((row_bytes + 1023) / 1024); strips <= out_w; ++strips) {
       const int32_t cols = (out_w + strips - 1) / strips;
       bool fits = true;
-      for (int32_t s = 0; s * cols < out_w && fits; ++s)
-        fits = gen_strip(p.ax, cols, p.align, s).len <= 1024;
+      for (int32_t s = 0; s * cols < out_w && fits; ++s) {
+        const GenStrip gs = gen_strip(p.ax, cols, p.align, s);
+        fits = s < kGenStrips && gs.len <= 1024;  // (base < row_bytes <= 16,384)
+        if (fits) p.gs.at[s] = (uint32_t)gs.base | ((uint32_t)gs.len << 16);
+      }
       if (!fits) continue;
       g.group_cols = cols;
       g.waves_per_frame = (out_w + cols - 1) / cols;
@@ -1119,17 +1146,14 @@ int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frame
     if (g.group_cols > 0) {
       g.chunk_bytes = 16;
       g.waves_per_block = g.waves_per_frame <= 4 ? g.waves_per_frame * (4 / g.waves_per_frame) : 4;
-      // bands of four output rows (the column table of the whole row is set up
-      // once per band), more when there are too few frames
+      // bands of four output rows, more when there are too few frames
       int64_t wb = (out_h + 4 - 1) / 4;
       const int64_t fill = (16384 + n * g.waves_per_frame - 1) / (n * g.waves_per_frame > 0 ? n * g.waves_per_frame : 1);
       if (fill > wb) wb = fill;
       if (wb > out_h) wb = out_h;
-      g.bands = (int32_t)wb;
       g.band_rows = (int32_t)((out_h + wb - 1) / wb);
-      const int64_t per_wave =
-          (64 * 16 * (p.packed ? 2 : 4) + (int64_t)g.band_rows * g.group_cols * 3 * 4 + 15) & ~(int64_t)15;
-      g.lds_bytes = (size_t)(out_w * 16 + g.waves_per_block * per_wave);
+      g.bands = (out_h + g.band_rows - 1) / g.band_rows;
+      g.lds_bytes = g.waves_per_block * gen_wave_lds(p.packed, g.band_rows, g.group_cols);
       p.gen = g.lds_bytes <= 64 * 1024;
       p.gg = g;
     }
@@ -1173,7 +1197,7 @@ int launch_area_sums(const AreaPlan& p, const uint8_t* frames, int64_t stride, i
     if (wblocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
 #define NSC_GEN_LAUNCH(PK, A)                                                                    \
   hipLaunchKernelGGL((k_area_sums_gen<PK, A>), dim3((unsigned)wblocks), dim3(64 * g.waves_per_block), \
-                     g.lds_bytes, stream, frames, stride, p.ay, p.ax, g, n, sums)
+                     g.lds_bytes, stream, frames, stride, p.ay, p.ax, g, p.gs, n, sums)
     if (p.align == 16) {
       if (p.packed) NSC_GEN_LAUNCH(true, 16); else NSC_GEN_LAUNCH(false, 16);
     } else if (p.align == 4) {

@@ -73,6 +73,14 @@ struct WaveGeom {
   size_t lds_bytes;         // dynamic LDS of a workgroup
 };
 
+// General column strips: first byte | bytes << 16 of each strip's part of a row.
+// (A strip of more than one column holds over 512 of a row's at most 16,384
+// bytes, one column alone only where two exceed 1,024.)
+constexpr int kGenStrips = 32;
+struct GenStrips {
+  uint32_t at[kGenStrips];
+};
+
 // Area-sum launch plan for one frame geometry.
 struct AreaPlan {
   Axis ay, ax;
@@ -87,6 +95,7 @@ struct AreaPlan {
   bool small;            // a whole frame in LDS (k_area_sums_small) for the plain sums
   bool gen;              // general strips (k_area_sums_gen) for the plain sums
   WaveGeom gg;           // their geometry: group_cols columns per strip
+  GenStrips gs;
 };
 int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frames,
                    int32_t out_h, int32_t out_w, int64_t n, AreaPlan* plan);

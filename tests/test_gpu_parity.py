@@ -115,6 +115,35 @@ def test_downsample_general_strips(H, W, Ho, Wo, pad, shift, n):
         assert np.array_equal(got[f], ref), f"frame {f}"
 
 
+@pytest.mark.parametrize("H,W,Ho,Wo,pad,shift,below", [
+    (96, 848, 50, 50, 0, 0, 199),    # 16-byte rows, bands of 4 rows with 2 left over
+    (96, 848, 50, 100, 12, 4, 6),    # 4-byte rows, padded
+    (40, 341, 7, 50, 5, 3, 27),      # any alignment
+    (31, 6, 3, 5, 0, 0, 1033),       # rows of 18 bytes: two chunks that overlap
+    (700, 340, 2, 17, 0, 0, 124),    # periodic 4-byte strips below; unpacked sums
+    (20, 1364, 20, 1364, 0, 0, 9),   # identity of a wide 4-byte row
+    (100, 100, 50, 50, 0, 0, 9),     # periodic 4-byte strips below, one strip per row
+])
+def test_downsample_general_strips_from(H, W, Ho, Wo, pad, shift, below):
+    """The last call size that leaves the general strips to the forms for few
+    output rows, the first that takes them, and twice that."""
+    fb = H * W * 3
+    stride = fb + pad
+    host = rng.integers(0, 256, size=(2 * below + 1) * stride + fb, dtype=np.uint8)
+    for n in (below, below + 1, 2 * below + 2):
+        end = (n - 1) * stride + fb
+        dev = torch.empty(shift + end, dtype=torch.uint8, device=DEV)[shift:]
+        dev.copy_(torch.from_numpy(host[:end]))
+        out = torch.full((n * Ho * Wo * 3 + 64,), -5, dtype=torch.int32, device=DEV)
+        nsc.nsc_downsample(dev, n, H, W, Ho, Wo, out, frame_stride=stride)
+        got = out.cpu().numpy()
+        assert (got[n * Ho * Wo * 3:] == -5).all()
+        got = got[:n * Ho * Wo * 3].reshape(n, Ho, Wo, 3)
+        for f in sorted({0, 1, n // 2, n - 1}):
+            ref = oracle.area_sums(host[f * stride:f * stride + fb].reshape(H, W, 3), Ho, Wo)
+            assert np.array_equal(got[f], ref), f"{n} frames, frame {f}"
+
+
 def test_downsample_extremes():
     # all-255 frames reach the largest sums; all-0 frames give zeros
     H, W = 720, 1280
