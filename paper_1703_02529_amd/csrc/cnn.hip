@@ -2109,7 +2109,9 @@ __global__ void __launch_bounds__(256)
 // First layer of a bf16 network that is fused with no second one (as the
 // pooling 64-channel one): the pre-processed bf16 input band in LDS, 8 bytes
 // per pixel, tiles and stores as in k_first_x3, two MFMAs per tile and 16
-// channels.  Stores fp32, or fp16 times the next layer's input scale.  Bound
+// channels; the bias is added to the finished sum, as in the other first
+// layers, so that it rounds as theirs do.  Stores fp32, or fp16 times the next
+// layer's input scale.  Bound
 // by the gather of the area sums and its latency.  1,501 images of 100x100
 // sums, 64 channels: 104 us against 125 with the weights in LDS and a
 // 2-byte store per value (k_conv_first).
@@ -2206,10 +2208,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       const bf16x8 x0 = ld(q + o0, q + o0b), x1 = ld(q + o1, q + o1b);
       f32x4 acc[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], x0, bias[nt]);
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], x0, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[1][nt], x1, acc[nt]);
-      // ReLU and pooling on the bits, as in k_first_x3
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[1][nt], x1, acc[nt]) + bias[nt];
+      // pooling on the bits, as in k_first_x3, the ReLU of the values that are stored
       int4 r[NT];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
@@ -2221,11 +2223,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
             v[k] = max(v[k], __builtin_amdgcn_update_dpp(0, v[k], kQuadXor1, 0xF, 0xF, true));
             v[k] = max(v[k], __builtin_amdgcn_update_dpp(0, v[k], kQuadXor2, 0xF, 0xF, true));
           }
-          v[k] = max(v[k], 0);
         }
         r[nt] = make_int4(v[0], v[1], v[2], v[3]);
       }
-      auto store = [&](int64_t at, const int4& v) {
+      auto store = [&](int64_t at, int4 v) {
+        v = make_int4(max(v.x, 0), max(v.y, 0), max(v.z, 0), max(v.w, 0));
         if (a.out_f16)
           *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(a.act_out) + at) =
               f16x4_bits(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z),

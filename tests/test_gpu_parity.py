@@ -340,6 +340,54 @@ def test_cnn_first_layer_alone_shapes(conv, pool, hw, fy):
     _cnn_case(spec, n_frames=16, n_img=1, fy=fy, max_count=2000)
 
 
+def _one_layer_logits(w, bias, S, pool=False, out=0, at=(2, 2), cout=16, den=1, bf16=True,
+                      pairs=False):
+    """Logits of a network of one conv layer whose dense layer passes the value
+    of channel `out` at (pooled) pixel `at` through: w [3][3][3] (dy, dx,
+    input channel) and bias of that channel; S: area sums [n][h][w][3]."""
+    n, h, wd, _ = S.shape
+    ho, wo = (h // 2, wd // 2) if pool else (h, wd)
+    conv = np.zeros((cout, 3, 3, 3), np.float32)
+    conv[out] = np.transpose(np.asarray(w, np.float32), (2, 0, 1))
+    cb = np.zeros(cout, np.float32)
+    cb[out] = bias
+    w1 = np.zeros((16, cout, ho, wo), np.float32)
+    w1[3, out, at[0], at[1]] = 1.0
+    w2 = np.zeros(16, np.float32)
+    w2[3] = 1.0
+    blob = np.concatenate([conv.ravel(), cb, w1.ravel(), np.zeros(16, np.float32), w2,
+                           np.zeros(1, np.float32)])
+    return _net_logits((cout,), (pool,), blob, S, den, bf16, pairs)
+
+
+def _net_logits(conv, pool, blob, S, den=1, bf16=False, pairs=False):
+    n, h, w, _ = S.shape
+    cnn = nsc.Cnn(nsc.make_desc(conv, pool, 16, h, w, bf16, pairs), blob)
+    ws = torch.empty(nsc.nsc_cnn_workspace_bytes(cnn, n), dtype=torch.uint8, device=DEV)
+    logit = torch.full((n,), 77.0, dtype=torch.float32, device=DEV)
+    nsc.nsc_specialized_cnn(cnn, _dev(S.astype(np.int32).reshape(-1)), h, w, den,
+                            torch.arange(n, dtype=torch.int32, device=DEV),
+                            torch.tensor([n], dtype=torch.int32, device=DEV), n, logit, ws)
+    got = logit.cpu().numpy()
+    cnn.close()
+    return got
+
+
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("cout", [16, 64, 128])
+@pytest.mark.parametrize("pairs", [False, True], ids=["fp16-acts", "bf16-pairs"])
+def test_cnn_first_layer_bias_is_added_last(pool, cout, pairs):
+    """Two products of 2^20 that cancel across the matrix steps leave the bias
+    as it is: its value then only rounds on the way into the dense layer, to 11
+    bits (fp16) or 16 (a pair of bf16).  Added to the first product it would
+    keep steps of 2^-3."""
+    w = np.zeros((3, 3, 3))
+    w[0, 0, 0], w[2, 1, 0] = 2.0 ** 20, -2.0 ** 20
+    S = np.full((3, 8, 8, 3), 255)
+    got = _one_layer_logits(w, 0.1, S, pool=pool, out=cout - 3, cout=cout, pairs=pairs)
+    assert np.abs(got / np.float32(0.1) - 1).max() <= (2.0 ** -16 if pairs else 2.0 ** -11), got
+
+
 @pytest.mark.parametrize("conv,pool,hw,fy", [
     ((64, 64), (False, True), (13, 9), 1),                 # fused 64-channel pair, ragged tiles
     ((64, 32, 64), (False, False, True), (23, 31), 1),     # fused pair into 32 channels
