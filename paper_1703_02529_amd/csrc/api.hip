@@ -1,6 +1,7 @@
 // Entry points of libnsc (declared in include/nsc.h): argument validation on
 // the host, workspace layout, weight packing and the ordering of the kernels
 // of the cascade on one stream.
+#include <float.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -424,6 +425,16 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
   std::vector<float> w2(p, p + c.dense);
   p += c.dense;
   c.b2 = *p;
+  // whether the first layer's sums (inputs within [-1, 1]) stay clear of the
+  // largest fp32 value, in any order and with weights rounded to bf16 (false
+  // for NaN and infinite weights)
+  c.overflow = 0;
+  for (int o = 0; o < c.layers[0].cout; ++o) {
+    double sum = fabs((double)convb[o]);
+    for (int k = 0; k < c.layers[0].kpad; ++k)
+      sum += fabs((double)convw[(size_t)o * c.layers[0].kpad + k]);
+    if (!(sum < 0.25 * FLT_MAX)) c.overflow = 1;
+  }
   // bf16: the conv weights again in MFMA fragment order (see CnnLayer)
   std::vector<float> convwf(c.bf16 ? conv_elems : 0, 0.0f);
   if (c.bf16) {
@@ -533,6 +544,7 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
   if (!c.bf16) {
     auto part = [](float v, int plane) -> uint16_t {
       uint32_t u = 0;
+      if (isnan(v)) return plane == 0 ? 0x7FC0 : 0;
       for (int p = 0; p <= plane; ++p) {
         if (p > 0 && !isfinite(v)) return 0;  // an infinite weight has no remainder
         memcpy(&u, &v, 4);
@@ -1265,6 +1277,7 @@ int nsc_group_create(const nsc_cascade_cfg* cfgs, const nsc_cnn* const* cnns, in
     t.c_low = k.c_low;
     t.c_high = k.c_high;
     t.b2 = cnns[c]->c.b2;
+    t.overflow = cnns[c]->c.overflow;
     hn[c] = t;
   }
   const size_t diff_bytes = align_up(sizeof(CamDiff) * (size_t)n_cams, kAlign);

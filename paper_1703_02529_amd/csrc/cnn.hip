@@ -291,6 +291,7 @@ struct ConvArgs {
   int32_t out_f16;          // act_out gets fp16 values times the next layer's input scale
   const CamNet* nets;       // camera group: per-camera weight offsets (else null)
   int64_t per_cam;          // frames per camera of a group
+  int32_t overflow;         // Cnn::overflow (one network; a group's cameras hold their own)
 };
 
 // Byte offset of survivor slot s's network from the base network's weights
@@ -302,6 +303,11 @@ __device__ __forceinline__ int64_t slot_woff(const CamNet* nets, int64_t per_cam
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)off);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(off >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+// Cnn::overflow of survivor slot s's network in a camera group.
+__device__ __forceinline__ bool slot_overflow(const CamNet* nets, int64_t per_cam,
+                                              const int32_t* idx, int64_t s) {
+  return __builtin_amdgcn_readfirstlane(nets[(uint32_t)idx[s] / (uint32_t)per_cam].overflow) != 0;
 }
 template <typename P>
 __device__ __forceinline__ const P* at_off(const P* p, int64_t off) {
@@ -1701,8 +1707,7 @@ k_pair64(ConvArgs a0, ConvArgs a1, Band64 b, const uint2* __restrict__ xin, int3
 // Weights are split on the host, in fragment order.
 
 // The three bf16 parts of 8 fp32 values, packed (0 remainders for infinities
-// and NaN; a sum that an infinite value reaches is infinite or, where a part of
-// its weight is zero, NaN).
+// and NaN).
 __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& h, uint4& m,
                                        uint4& l) {
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
@@ -1732,6 +1737,19 @@ __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& 
 // network 1.90 ms against 27.4, whose weights left room for one tile row in
 // the LDS.
 constexpr int x3_tiles(int nt) { return nt <= 2 ? 4 : 3; }
+
+// The sum of the two accumulators.  Where an infinite operand made the first
+// one infinite or NaN it is the value the fp32 cores would give, and the second
+// holds infinity times the zero parts of the other operand.
+__device__ __forceinline__ f32x4 x3_sum(const f32x4& acc, const f32x4& lo) {
+  f32x4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float t = acc[e] + lo[e];
+    r[e] = fabsf(acc[e]) < INFINITY ? t : acc[e];
+  }
+  return r;
+}
 
 // Stages channels c0 .. c0 + 31 of band rows [0, rows_used) into the planes.
 __device__ __forceinline__ void stage_x3(const float* __restrict__ src, int cin, int c0,
@@ -1910,7 +1928,7 @@ k_conv_x3(ConvArgs a, Band64 b) {
         int r, x;
         const bool in = i < mt && band_pixel(t0 + wave + kBandWaves * i, m, a.pool, rows, wn, r, x);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[i][nt] += lo[i][nt];
+        for (int nt = 0; nt < NT; ++nt) acc[i][nt] = x3_sum(acc[i][nt], lo[i][nt]);
         if (i < mt)  // uniform
           band64_epilogue<NT>(acc[i], bp, 1.0f, 1.0f, out, a.cout, in ? 4 * ty0 + r : b.h, x, b.h,
                               b.w, a.pool, m, false);
@@ -1984,6 +2002,7 @@ __global__ void __launch_bounds__(256)
   f32x4 bias[NT];
   int64_t w_off = 0;
   int w_grp = -1;
+  bool ovf = a.overflow != 0;
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t s = item / (bands * ngrp);
     const int bg = (int)(item - s * (bands * ngrp));
@@ -2001,6 +2020,7 @@ __global__ void __launch_bounds__(256)
       const float* bp = at_off(a.bias, off) + grp * NT * 16 + 4 * g;
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(bp + nt * 16);
+      if constexpr (G) ovf = slot_overflow(a.nets, a.per_cam, a.idx, s);
       w_off = off;
       w_grp = grp;
     }
@@ -2062,7 +2082,18 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[0][nt], xm, lo[nt]);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] += X::mma(w[4][nt], yhm, lo[nt]);
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[4][nt], yhm, lo[nt]);
+      if (ovf) {  // uniform: infinities as on the fp32 cores, NaN as 0
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          acc[nt] = x3_sum(acc[nt], lo[nt]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[nt][e] = fmaxf(acc[nt][e], 0.0f);
+        }
+      } else {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt] += lo[nt];
+      }
       // ReLU and pooling on the bits: as signed integers the positive floats
       // order like their values, above every negative one
       int4 r[NT];
@@ -2157,6 +2188,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
   int64_t w_off = 0;
   int w_grp = -1;
   float st16 = 0.0f;
+  bool ovf = a.overflow != 0;
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t s = item / (bands * ngrp);
     const int bg = (int)(item - s * (bands * ngrp));
@@ -2175,6 +2207,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(bp + nt * 16);
       if (a.out_f16) st16 = at_off(a.scl, off)[2];
+      if constexpr (G) ovf = slot_overflow(a.nets, a.per_cam, a.idx, s);
       w_off = off;
       w_grp = grp;
     }
@@ -2211,6 +2244,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], x0, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[1][nt], x1, acc[nt]) + bias[nt];
+      if (ovf) {  // uniform: NaN as 0, before the pooling
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[nt][k] = fmaxf(acc[nt][k], 0.0f);
+      }
       // pooling on the bits, as in k_first_x3, the ReLU of the values that are stored
       int4 r[NT];
 #pragma unroll
@@ -3389,6 +3428,7 @@ int run_cnn(const Cnn& cnn, const CnnRunArgs& r, void* ws, size_t ws_bytes, hipS
     a.scl = cnn.scales + 2 * l;
     a.nets = r.nets;
     a.per_cam = r.per_cam;
+    a.overflow = cnn.overflow;
     return a;
   };
   // weights in fragment order for the banded kernels (bf16; scaled fp16 for

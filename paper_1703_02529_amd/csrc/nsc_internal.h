@@ -280,6 +280,8 @@ struct Cnn {
   float* scales;            // [2 (n_layers + 1)]: per layer, then the dense layer, the fp16
                             // path's input scale 2^-aexp and output scale 2^(aexp - wexp)
   float b2;
+  int32_t overflow;         // a sum of the first layer may reach infinity or NaN (huge, infinite
+                            // or NaN weights), for the kernels whose fast form holds no such sums
   size_t act_elems;         // largest per-image activation (elements)
 };
 // One camera's network in a camera group: the group's networks share one
@@ -290,7 +292,7 @@ struct CamNet {
   int64_t woff;
   double c_low, c_high;
   float b2;
-  int32_t pad;
+  int32_t overflow;         // Cnn::overflow of the camera's network
 };
 
 struct CnnRunArgs {

@@ -388,6 +388,62 @@ def test_cnn_first_layer_bias_is_added_last(pool, cout, pairs):
     assert np.abs(got / np.float32(0.1) - 1).max() <= (2.0 ** -16 if pairs else 2.0 ** -11), got
 
 
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("kind", ["pairs", "f32"])
+def test_cnn_first_layer_overflow(kind, pool):
+    """Sums that are NaN count as 0 in the ReLU, and an infinite sum stays
+    infinite, also where it meets zero parts of an operand."""
+    form = dict(bf16=kind == "pairs", pairs=kind == "pairs", pool=pool)
+    inf = np.float32(np.inf)
+    w = np.zeros((3, 3, 3))
+    w[0, 0, 0], w[2, 1, 0] = inf, -inf   # inf - inf, or inf * 0 past the border
+    S = np.full((2, 8, 8, 3), 510)
+    S[1] = 255                           # the input 0 (den 2)
+    got = _one_layer_logits(w, 0.5, S, den=2, **form)
+    assert (got == 0).all(), got
+    if kind == "f32":
+        # one pixel meets the infinite weight with 1, every other one with 0
+        w = np.zeros((3, 3, 3))
+        w[1, 1, 0] = inf
+        S = np.full((3, 8, 8, 3), 255)
+        S[0, 4, 4, 0] = 510
+        S[1, 4, 4, 0] = 0                # -inf: 0
+        got = _one_layer_logits(w, 0.5, S, den=2, out=5, at=(2, 2) if pool else (4, 4), **form)
+        assert list(got) == [inf, 0, 0], got
+        # finite weights whose sum overflows
+        w[1, 1, 0] = w[1, 1, 1] = 3e38
+        S[0, 4, 4] = 510
+        S[1, 4, 4, 2] = S[2, 4, 4, 0] = 510
+        S[1, 4, 4, 0] = 255
+        got = _one_layer_logits(w, 0.5, S, den=2, out=5, at=(2, 2) if pool else (4, 4), **form)
+        assert list(got) == [inf, 0.5, np.float32(3e38)], got
+
+
+@pytest.mark.parametrize("w2", [0.5, 0.3], ids=["one-part", "three-parts"])
+@pytest.mark.parametrize("pool", [False, True])
+def test_cnn_fp32_inner_layer_overflow(pool, w2):
+    """An activation that overflows in the first fp32 layer keeps its sums of
+    the second one infinite, whatever parts the weight has."""
+    S = np.full((2, 8, 8, 3), 255)
+    S[0, 4, 4, 0] = 510
+    conv0 = np.zeros((32, 3, 3, 3), np.float32)
+    conv0[7, 0, 1, 1] = 3e38
+    b0 = np.zeros(32, np.float32)
+    b0[7] = 3e38
+    conv1 = np.zeros((32, 32, 3, 3), np.float32)
+    conv1[20, 7, 1, 1] = w2
+    o = 4 if pool else 8
+    w1 = np.zeros((16, 32, o, o), np.float32)
+    w1[3, 20, o // 2, o // 2] = 1.0
+    out = np.zeros(16, np.float32)
+    out[3] = 1.0
+    blob = np.concatenate([conv0.ravel(), b0, conv1.ravel(), np.zeros(32, np.float32), w1.ravel(),
+                           np.zeros(16, np.float32), out, np.zeros(1, np.float32)])
+    got = _net_logits((32, 32), (False, pool), blob, S, den=2)
+    assert got[0] == np.inf
+    assert abs(float(got[1]) / (float(np.float32(3e38)) * float(np.float32(w2))) - 1) <= 2.0 ** -20
+
+
 @pytest.mark.parametrize("conv,pool,hw,fy", [
     ((64, 64), (False, True), (13, 9), 1),                 # fused 64-channel pair, ragged tiles
     ((64, 32, 64), (False, False, True), (23, 31), 1),     # fused pair into 32 channels

@@ -140,3 +140,25 @@ def test_group_tiles_of_many_cameras(cams, n):
         assert torch.allclose(got[fired], want[fired], rtol=1e-5, atol=1e-5)
         r.close()
     group.close()
+
+
+def test_group_with_a_network_that_overflows():
+    """One camera's fp32 network has infinite first-layer weights: its frames
+    and its neighbours' come out as in their own cascades."""
+    wls = [_workload(1) for _ in range(3)]
+    for w in wls:
+        w.cnn.bf16 = False
+    blobs = [_blob(c) for c in range(3)]
+    blobs[1][[0, 9, 31]] = np.inf, -np.inf, np.nan
+    videos = [_frames(40, c, rate=0.5) for c in range(3)]
+    group = GroupRunner(wls, blobs, 40)
+    group.run(torch.cat(videos), 40, t0=0)
+    for c in range(3):
+        r = CascadeRunner(wls[c], blobs[c], 40)
+        r.run(videos[c], 40, t0=0)
+        got, want = group.logit[c * 40:(c + 1) * 40], r.logit[:40]
+        fired = r.fire[:40] == 1
+        assert fired.sum() > 5 and not torch.isnan(want[fired]).any()
+        assert torch.allclose(got[fired], want[fired], rtol=1e-5, atol=1e-5)
+        r.close()
+    group.close()
