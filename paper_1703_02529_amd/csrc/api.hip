@@ -538,32 +538,33 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
               w1f[(((size_t)ks * nts + nt) * 64 + lane) * 8 + e] = w1h[(size_t)u * c.flat + k];
           }
   }
-  // fp32 networks: every conv weight as three bf16 parts (their sum, split by
-  // truncation), in the fragment orders of k_first_x3 and k_conv_x3
+  // fp32 networks: every conv weight as three bf16 parts (their sum; the first
+  // two rounded to nearest), in the fragment orders of k_first_x3 and k_conv_x3
   std::vector<uint16_t> convwx;
   if (!c.bf16) {
     auto part = [](float v, int plane) -> uint16_t {
-      uint32_t u = 0;
       if (isnan(v)) return plane == 0 ? 0x7FC0 : 0;
-      for (int p = 0; p <= plane; ++p) {
-        if (p > 0 && !isfinite(v)) return 0;  // an infinite weight has no remainder
+      if (isinf(v)) return plane == 0 ? host_bf16(v) : 0;
+      float h = host_bf16_value(v);
+      if (isinf(h)) {  // cut off what rounding would take to infinity
+        uint32_t u;
         memcpy(&u, &v, 4);
         u &= 0xFFFF0000u;
-        float t;
-        memcpy(&t, &u, 4);
-        if (p < plane) v = isfinite(v) ? v - t : INFINITY;
+        memcpy(&h, &u, 4);
       }
-      return (uint16_t)(u >> 16);
+      if (plane == 0) return host_bf16(h);
+      const float r = v - h;
+      return plane == 1 ? host_bf16(r) : host_bf16(r - host_bf16_value(r));
     };
     for (int l = 0; l < c.n_layers; ++l) {
       CnnLayer& L = c.layers[l];
       const int nts = L.cout / 16;
       L.wx_off = convwx.size();
       if (l == 0) {
-        convwx.resize(L.wx_off + (size_t)6 * nts * 512, 0);
-        // step 1: lane groups 0, 1 hold plane lo[q] and 2, 3 plane hi[q] of dy = 2
-        const int lo[3] = {0, 1, 2}, hi[3] = {1, 0, 0};
-        for (int q = 0; q < 6; ++q)
+        convwx.resize(L.wx_off + (size_t)7 * nts * 512, 0);
+        // step 1: lane groups 0, 1 hold plane lo[q] and 2, 3 plane hi[q] of dy = 2 (-1: zeros)
+        const int lo[4] = {0, 1, 2, -1}, hi[4] = {-1, 0, 0, 1};
+        for (int q = 0; q < 7; ++q)
           for (int nt = 0; nt < nts; ++nt)
             for (int lane = 0; lane < 64; ++lane)
               for (int e = 0; e < 8; ++e) {
@@ -571,7 +572,7 @@ int nsc_cnn_create(const nsc_cnn_desc* desc, const float* hw, int64_t n_floats, 
                 const int k = q < 3 ? g * 8 + e : 32 + (g & 1) * 8 + e;
                 const int plane = q < 3 ? q : (g < 2 ? lo[q - 3] : hi[q - 3]);
                 convwx[L.wx_off + (((size_t)q * nts + nt) * 64 + lane) * 8 + e] =
-                    part(convw[L.w_off + (size_t)o * L.kpad + k], plane);
+                    plane < 0 ? 0 : part(convw[L.w_off + (size_t)o * L.kpad + k], plane);
               }
       } else if (L.cin % 32 == 0) {
         convwx.resize(L.wx_off + (size_t)3 * L.cout * 9 * L.cin);

@@ -1692,38 +1692,69 @@ k_pair64(ConvArgs a0, ConvArgs a1, Band64 b, const uint2* __restrict__ xin, int3
 
 // ------------------------------------------ fp32 layers on the bf16 cores
 //
-// An fp32 network's conv layers run on the bf16 matrix cores without giving
-// up fp32 operands: every fp32 value is the exact sum of three bf16 values
-// (8 significant bits each, split by truncation), and a product takes the six
-// of the nine partial products that reach 2^-16 of it,
+// An fp32 network's conv layers run on the bf16 matrix cores with fp32
+// operands: every fp32 value is the exact sum of three bf16 values h + m + l
+// (8 significant bits each, h and m rounded to nearest, so that |m| <= 2^-8 and
+// |l| <= 2^-17 of the value, of either sign), and a product takes six of the
+// nine partial products,
 //   h h', h m', m h', h l', l h', m m',
-// each exact in the fp32 accumulation; the three left out are below 2^-22 of
-// the product together.  The first goes into one accumulator and the five
-// small ones into another, added at the end, so a sum rounds once per 32
-// products where v_mfma_f32_16x16x4_f32 rounds once per 4.  Error of the
-// logits against fp64 (2-norm, random He-normal networks on 50x50 inputs):
-// 32-32 channels 2.8e-7 against 4.2e-7 on the fp32 cores, 64-64-64-64
-// 4.7e-7 against 8.8e-7, and below theirs in all seven networks compared.
+// each exact in the fp32 accumulation; the three left out, m l', l m' and l l',
+// are together at most 2^-24 of the product (an fp32 product's own rounding)
+// and of either sign.  (Parts split by truncation left out up to 2^-21, always
+// towards zero.)  The first product goes into one accumulator and the five
+// small ones into another, which also holds the first layer's bias, added at the
+// end, so a sum rounds once per 32 products where v_mfma_f32_16x16x4_f32 rounds
+// once per 4.  Measured rms error over the sum of the products' magnitudes,
+// against those cores: 27 normal products of the first layer 0.87e-8 against
+// 2.58e-8, 3 positive ones 2.56e-8 against 3.40e-8, 8 and 243 live of 288
+// positive ones of an inner layer 2.69e-8 against 4.57e-8 and 0.83e-7 against
+// 2.18e-7; a single product, which they round once, 2.61e-8 against 2.53e-8.
 // Weights are split on the host, in fragment order.
 
-// The three bf16 parts of 8 fp32 values, packed (0 remainders for infinities
-// and NaN).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Two fp32 values rounded to bf16 (nearest even), packed.
+__device__ __forceinline__ uint32_t bf16x2_bits(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+// The upper halves of two fp32 values, packed.
+__device__ __forceinline__ uint32_t upper2(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+__device__ __forceinline__ float lo_f32(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); }
+
+// The first part of two values that rounding could take to infinity: cut off
+// from 0x7F7F8000 on (infinity stays), else rounded.
+__device__ __forceinline__ uint32_t split_large(float a, float b) {
+  auto part = [](float v) {
+    const uint32_t u = __float_as_uint(v);
+    return (u & 0x7FFFFFFFu) >= 0x7F7F8000u ? u >> 16 : (uint32_t)f32_to_bf16_bits(v);
+  };
+  return part(a) | (part(b) << 16);
+}
+
+// The three bf16 parts of 8 fp32 values, packed.  LARGE: some value is at least
+// 0x7F7F8000 (0 remainders for infinity).
+template <bool LARGE>
 __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& h, uint4& m,
                                        uint4& l) {
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  uint32_t hb[8], mb[8], lb[8];
+  uint32_t hw[4], mw[4], lw[4];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    hb[e] = __float_as_uint(v[e]) & 0xFFFF0000u;
-    float r = v[e] - __uint_as_float(hb[e]);
-    r = r == r ? r : 0.0f;
-    mb[e] = __float_as_uint(r) & 0xFFFF0000u;
-    lb[e] = __float_as_uint(r - __uint_as_float(mb[e]));
+  for (int e = 0; e < 4; ++e) {
+    hw[e] = LARGE ? split_large(v[2 * e], v[2 * e + 1]) : bf16x2_bits(v[2 * e], v[2 * e + 1]);
+    float r0 = v[2 * e] - lo_f32(hw[e]), r1 = v[2 * e + 1] - hi_f32(hw[e]);
+    if constexpr (LARGE) {  // infinity less infinity
+      r0 = r0 == r0 ? r0 : 0.0f;
+      r1 = r1 == r1 ? r1 : 0.0f;
+    }
+    mw[e] = bf16x2_bits(r0, r1);
+    lw[e] = upper2(r0 - lo_f32(mw[e]), r1 - hi_f32(mw[e]));
   }
-  auto pack = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };
-  h = make_uint4(pack(hb[0], hb[1]), pack(hb[2], hb[3]), pack(hb[4], hb[5]), pack(hb[6], hb[7]));
-  m = make_uint4(pack(mb[0], mb[1]), pack(mb[2], mb[3]), pack(mb[4], mb[5]), pack(mb[6], mb[7]));
-  l = make_uint4(pack(lb[0], lb[1]), pack(lb[2], lb[3]), pack(lb[4], lb[5]), pack(lb[6], lb[7]));
+  h = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+  m = make_uint4(mw[0], mw[1], mw[2], mw[3]);
+  l = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
 // Inner layers (input channels a multiple of 32), banded as the 64-channel
@@ -1739,15 +1770,14 @@ __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& 
 constexpr int x3_tiles(int nt) { return nt <= 2 ? 4 : 3; }
 
 // The sum of the two accumulators.  Where an infinite operand made the first
-// one infinite or NaN it is the value the fp32 cores would give, and the second
-// holds infinity times the zero parts of the other operand.
-__device__ __forceinline__ f32x4 x3_sum(const f32x4& acc, const f32x4& lo) {
+// one infinite or NaN it is the value the fp32 cores would give (plus the bias
+// that the second one started with), and the second holds infinity times the
+// zero parts of the other operand.
+__device__ __forceinline__ f32x4 x3_sum(const f32x4& acc, const f32x4& lo,
+                                        const f32x4& bias = f32x4{0.f, 0.f, 0.f, 0.f}) {
   f32x4 r;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float t = acc[e] + lo[e];
-    r[e] = fabsf(acc[e]) < INFINITY ? t : acc[e];
-  }
+  for (int e = 0; e < 4; ++e) r[e] = acc[e] + (fabsf(acc[e]) < INFINITY ? lo[e] : bias[e]);
   return r;
 }
 
@@ -1775,15 +1805,31 @@ __device__ __forceinline__ void stage_x3(const float* __restrict__ src, int cin,
         v[j][1] = *reinterpret_cast<const float4*>(p + 4);
       }
     }
+    // activations are not negative (and not NaN): their bits order like them
+    int mx = 0;
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-      if (addr[j] < 0) continue;
-      uint4 h, m, l;
-      split3(v[j][0], v[j][1], h, m, l);
-      *reinterpret_cast<uint4*>(lds + addr[j]) = h;
-      *reinterpret_cast<uint4*>(lds + b.lo_bytes + addr[j]) = m;
-      *reinterpret_cast<uint4*>(lds + 2 * b.lo_bytes + addr[j]) = l;
-    }
+    for (int j = 0; j < B; ++j)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float4& f = v[j][k];
+        mx = max(mx, max(max(__float_as_int(f.x), __float_as_int(f.y)),
+                         max(__float_as_int(f.z), __float_as_int(f.w))));
+      }
+    auto put = [&](auto large) {
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        if (addr[j] < 0) continue;
+        uint4 h, m, l;
+        split3<decltype(large)::value>(v[j][0], v[j][1], h, m, l);
+        *reinterpret_cast<uint4*>(lds + addr[j]) = h;
+        *reinterpret_cast<uint4*>(lds + b.lo_bytes + addr[j]) = m;
+        *reinterpret_cast<uint4*>(lds + 2 * b.lo_bytes + addr[j]) = l;
+      }
+    };
+    if (mx >= 0x7F7F8000)
+      put(std::true_type());
+    else
+      put(std::false_type());
   }
 }
 
@@ -1941,11 +1987,12 @@ k_conv_x3(ConvArgs a, Band64 b) {
 // become fp32 inputs, each pixel 24 bytes of LDS: the h, m and l parts of its
 // 4 channels (the fourth 0), read 8 bytes at a time (see opaque()).  K is (dy, dx of 4, c of 4) = 48 of 64: a first MFMA step takes dy 0
 // and 1, and the half-used second one (dy 2) carries a second partial product
-// in its upper half (pairs h h' | m m', h m' | m h', h l' | l h'), so a tile
-// takes 9 MFMAs per 16 channels.  Pixels run along the band in raster order
+// in its upper half (h h' alone, whose accumulator then holds it exactly, pairs
+// h m' | m h' and h l' | l h', and m m'), so a tile takes 10 MFMAs per 16
+// channels.  Pixels run along the band in raster order
 // (4 pooling windows per tile on a pooling layer), the lane's position
 // carried from tile to tile.  Bound by instruction issue (45 vector
-// instructions and 18 MFMAs per tile) and the input gather's latency.  3,000
+// instructions and 20 MFMAs per tile) and the input gather's latency.  3,000
 // images of 50x50, 32 channels: 150 us against 335 on the fp32 cores.
 struct FirstX3 {
   int32_t bw;          // staged pixels per band row (image columns -1 .. bw - 2)
@@ -1997,8 +2044,8 @@ __global__ void __launch_bounds__(256)
     const uint2 q = *reinterpret_cast<const uint2*>(lds + addr + kPix);
     return __builtin_bit_cast(bf16x8, make_uint4(p.x, p.y, q.x, q.y));
   };
-  // fragments [3 planes of step 0, then the 3 pairs of step 1][output block]
-  bf16x8 w[6][NT];
+  // fragments [3 planes of step 0, then 4 of step 1][output block]
+  bf16x8 w[7][NT];
   f32x4 bias[NT];
   int64_t w_off = 0;
   int w_grp = -1;
@@ -2014,7 +2061,7 @@ __global__ void __launch_bounds__(256)
     if (off != w_off || grp != w_grp) {  // uniform: once without groups
       const bf16x8* wf = at_off(reinterpret_cast<const bf16x8*>(a.wts), off) + grp * NT * 64 + lane;
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int q = 0; q < 7; ++q)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) w[q][nt] = wf[(q * ntw + nt) * 64];
       const float* bp = at_off(a.bias, off) + grp * NT * 16 + 4 * g;
@@ -2044,7 +2091,7 @@ __global__ void __launch_bounds__(256)
           for (int k = 0; k < 3; ++k) v[k] = (float)(fma(2.0, (double)c[k], -den) * f.inv255);
         }
         uint4 h, mm, l;
-        split3(make_float4(v[0], v[1], v[2], 0.f), make_float4(0.f, 0.f, 0.f, 0.f), h, mm, l);
+        split3<false>(make_float4(v[0], v[1], v[2], 0.f), make_float4(0.f, 0.f, 0.f, 0.f), h, mm, l);
         uint2* d = reinterpret_cast<uint2*>(lds + p * kPix);
         d[0] = make_uint2(h.x, h.y);
         d[1] = make_uint2(mm.x, mm.y);
@@ -2066,9 +2113,9 @@ __global__ void __launch_bounds__(256)
       const bf16x8 yhm = ld(q + o1m), yhl = ld(q + o1l);
       f32x4 acc[NT], lo[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[1][nt], xm, f32x4{0.f, 0.f, 0.f, 0.f});
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[1][nt], xm, bias[nt]);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], xh, bias[nt]);
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = X::mma(w[0][nt], xh, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[2][nt], xh, lo[nt]);
 #pragma unroll
@@ -2083,10 +2130,12 @@ __global__ void __launch_bounds__(256)
       for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[0][nt], xm, lo[nt]);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[4][nt], yhm, lo[nt]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) lo[nt] = X::mma(w[6][nt], yhm, lo[nt]);
       if (ovf) {  // uniform: infinities as on the fp32 cores, NaN as 0
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-          acc[nt] = x3_sum(acc[nt], lo[nt]);
+          acc[nt] = x3_sum(acc[nt], lo[nt], bias[nt]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[nt][e] = fmaxf(acc[nt][e], 0.0f);
         }

@@ -267,7 +267,7 @@ struct Cnn {
   void* w1h;                // bf16 networks: dense weights as fp16 times 2^dense_wexp
   void* conv_w0h;           // fp16 path: k_pair64's first layer, scaled, bias folded in (or null)
   void* conv_wx;            // fp32 networks: conv weights as three bf16 parts each, in fragment
-                            // order (first layer: [3 planes of K step 0, 3 pairs of step 1][nt];
+                            // order (first layer: [3 planes of K step 0, 4 of step 1][nt];
                             // inner layers of 32 k input channels: [channel block][tap][plane][nt])
   void* w1f;                // fp16 path: w1h in fragment order, padded to whole chunks
   int32_t dense_wexp, dense_aexp;  // as CnnLayer::wexp / aexp, for the dense layer

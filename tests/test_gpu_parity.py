@@ -389,6 +389,101 @@ def test_cnn_first_layer_bias_is_added_last(pool, cout, pairs):
 
 
 @pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("cout", [16, 32, 48])
+def test_cnn_fp32_first_layer_bias(pool, cout):
+    """The same in an fp32 network: the bias comes out to the bit."""
+    w = np.zeros((3, 3, 3))
+    w[0, 0, 0], w[2, 1, 0] = 2.0 ** 20, -2.0 ** 20
+    S = np.full((3, 8, 8, 3), 255)
+    got = _one_layer_logits(w, 0.1, S, pool=pool, out=cout - 3, cout=cout, bf16=False)
+    assert (got == np.float32(0.1)).all(), got
+
+
+def _operands(r, k, kind):
+    if kind == "normal":
+        return r.standard_normal(k).astype(np.float32)
+    if kind == "positive":
+        return r.uniform(0.01, 1, k).astype(np.float32)
+    return (1 + r.integers(1, 128, k) / 128 - 2.0 ** -23).astype(np.float32)  # low bits all set
+
+
+def _check_fp32_sums(got, terms, single):
+    """Errors of sums of products (terms [n][k], exact in fp64), relative to
+    the sum of their magnitudes: no larger than those of a chain of fp32 fused
+    multiply-adds, and of no preferred sign (the mean of n errors of either
+    sign stays within four of its standard deviations).  A single product,
+    rounded once by the chain, may leave out 2^-24 more of itself."""
+    exact, scale = terms.sum(1), np.abs(terms).sum(1)
+    chain = np.zeros(len(terms), np.float32)
+    for k in range(terms.shape[1]):
+        chain = (chain.astype(np.float64) + terms[:, k]).astype(np.float32)
+    ok = exact > 1e-3 * scale  # past the ReLU
+    e = ((got - exact) / scale)[ok]
+    rms = np.sqrt((e ** 2).mean())
+    ref = np.sqrt((((chain - exact) / scale)[ok] ** 2).mean())
+    print(f"rms {rms:.3e} against {ref:.3e}, mean {e.mean():+.2e}, largest {np.abs(e).max():.2e}")
+    assert rms <= (np.hypot(ref, 2.0 ** -25 * np.sqrt(2 / 3)) if single else ref)
+    assert abs(e.mean()) <= 4 * rms / np.sqrt(e.size)
+    if single:
+        assert np.abs(e).max() <= 2.0 ** -23 * (1 + 2.0 ** -7)
+
+
+DENQ = 8000
+
+
+def _fine_inputs(r, n, positive):
+    S = r.integers(DENQ * 255 // 2 + 1 if positive else 0, DENQ * 255 + 1, size=(n, 6, 6, 3))
+    return S, ((2 * S - 255 * DENQ) / (255 * DENQ)).astype(np.float32)
+
+
+@pytest.mark.parametrize("live", [1, 3, 9, 27])
+@pytest.mark.parametrize("kind", ["normal", "positive", "lowbits"])
+def test_cnn_fp32_first_layer_sums(kind, live):
+    r = np.random.default_rng([live, len(kind)])
+    got, terms = [], []
+    for _ in range(4):
+        S, x = _fine_inputs(r, 4096, kind != "normal")
+        w = np.zeros(27, np.float32)
+        w[r.choice(27, live, replace=False)] = _operands(r, live, kind)
+        got.append(_one_layer_logits(w.reshape(3, 3, 3), 0.0, S, out=5, at=(3, 2), den=DENQ,
+                                     bf16=False))
+        t = x[:, 2:5, 1:4].reshape(-1, 27).astype(np.float64) * w
+        terms.append(t[:, w != 0])
+    _check_fp32_sums(np.concatenate(got), np.concatenate(terms), live == 1)
+
+
+@pytest.mark.parametrize("live", [1, 8, 32, 243])
+@pytest.mark.parametrize("kind", ["normal", "positive", "lowbits"])
+def test_cnn_fp32_inner_layer_sums(kind, live):
+    """The first layer copies each of the 27 neighbouring inputs (positive)
+    into a channel of its own, exactly; the second sums `live` products."""
+    r = np.random.default_rng([live, len(kind)])
+    copy = np.zeros((32, 3, 3, 3), np.float32)
+    for c in range(27):
+        copy[c, c % 3, c // 9, c // 3 % 3] = 1
+    w1 = np.zeros((16, 32, 6, 6), np.float32)
+    w1[3, 9, 3, 3] = 1
+    out = np.zeros(16, np.float32)
+    out[3] = 1
+    got, terms = [], []
+    for _ in range(4):
+        S, x = _fine_inputs(r, 4096, True)
+        w = np.zeros((32, 9), np.float32)
+        w.reshape(-1)[r.choice(27 * 9, live, replace=False)] = _operands(r, live, kind)
+        conv = np.zeros((32, 32, 3, 3), np.float32)
+        conv[9] = w.reshape(32, 3, 3)
+        blob = np.concatenate([copy.ravel(), np.zeros(32), conv.ravel(), np.zeros(32), w1.ravel(),
+                               np.zeros(16), out, np.zeros(1)]).astype(np.float32)
+        got.append(_net_logits((32, 32), (False, False), blob, S, den=DENQ))
+        xp = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+        act = np.stack([xp[:, 2 + c // 9:5 + c // 9, 2 + c // 3 % 3:5 + c // 3 % 3, c % 3]
+                        for c in range(27)], 1).astype(np.float64)  # [n][c][3][3] around (3, 3)
+        t = act.reshape(len(x), -1) * w[:27].reshape(-1)
+        terms.append(t[:, w[:27].reshape(-1) != 0])
+    _check_fp32_sums(np.concatenate(got), np.concatenate(terms), live == 1)
+
+
+@pytest.mark.parametrize("pool", [False, True])
 @pytest.mark.parametrize("kind", ["pairs", "f32"])
 def test_cnn_first_layer_overflow(kind, pool):
     """Sums that are NaN count as 0 in the ReLU, and an infinite sum stays
@@ -399,6 +494,9 @@ def test_cnn_first_layer_overflow(kind, pool):
     w[0, 0, 0], w[2, 1, 0] = inf, -inf   # inf - inf, or inf * 0 past the border
     S = np.full((2, 8, 8, 3), 510)
     S[1] = 255                           # the input 0 (den 2)
+    got = _one_layer_logits(w, 0.5, S, den=2, **form)
+    assert (got == 0).all(), got
+    w[0, 0, 0] = np.nan
     got = _one_layer_logits(w, 0.5, S, den=2, **form)
     assert (got == 0).all(), got
     if kind == "f32":
@@ -441,7 +539,11 @@ def test_cnn_fp32_inner_layer_overflow(pool, w2):
                            np.zeros(16, np.float32), out, np.zeros(1, np.float32)])
     got = _net_logits((32, 32), (False, pool), blob, S, den=2)
     assert got[0] == np.inf
-    assert abs(float(got[1]) / (float(np.float32(3e38)) * float(np.float32(w2))) - 1) <= 2.0 ** -20
+    assert abs(float(got[1]) / (float(np.float32(3e38)) * float(np.float32(w2))) - 1) <= 2.0 ** -23
+    # an activation that rounding to bf16 would take to infinity, without the overflow
+    blob[32 * 27 + 7] = 3.4e38
+    got = _net_logits((32, 32), (False, pool), blob, np.full((2, 8, 8, 3), 255), den=2)
+    assert np.abs(got / (float(np.float32(3.4e38)) * float(np.float32(w2))) - 1).max() <= 2.0 ** -23
 
 
 @pytest.mark.parametrize("conv,pool,hw,fy", [
