@@ -8,6 +8,7 @@ and fire flags bit-exact, logits within the network's tolerance, labels and
 defer flags exact outside the threshold band).
 """
 import dataclasses
+import types
 
 import numpy as np
 import pytest
@@ -225,3 +226,30 @@ def test_group_rejects_mixed_geometry_and_skipping():
     assert nsc.nsc_group_create_status([good, good], [cnn.handle, other.handle]) == -2
     cnn.close()
     other.close()
+
+
+@pytest.mark.parametrize("w,bf16", [(1200, False), (3504, True)])
+def test_group_first_layer_of_wide_maps(w, bf16):
+    """Cameras whose first layer is too wide for the kernels of usual widths,
+    each with its own weights, as in the camera's own cascade."""
+    h, n, conv = 4, 3, 16
+    wl = types.SimpleNamespace(
+        video=types.SimpleNamespace(h=h, w=w), dd_h=h, dd_w=w,
+        cnn=types.SimpleNamespace(in_h=h, in_w=w, conv=[conv], pool=[True], dense=16, bf16=bf16),
+        ref_mode=nsc.NSC_REF_PREV, delta=1, grid=(1, 1), delta_diff=0.0, c_low=0.2, c_high=0.8,
+        lr_bias=0.0)
+    size = 27 * conv + conv + 16 * conv * (h // 2) * (w // 2) + 16 + 16 + 1
+    r = np.random.default_rng(w)
+    blobs = [r.normal(0, 0.05, size).astype(np.float32) for _ in range(3)]
+    frames = torch.from_numpy(r.integers(0, 256, (3, n, h, w, 3), dtype=np.uint8)).to(DEV)
+    group = GroupRunner([wl] * 3, blobs, n)
+    group.run(frames, n, t0=0)
+    for c in range(3):
+        one = CascadeRunner(wl, blobs[c], n)
+        one.run(frames[c], n, t0=0)
+        got, want = group.logit[c * n:(c + 1) * n], one.logit[:n]
+        assert bool((one.fire[:n] == 1).all())
+        # (the dense layer's fp32 sums of 19,200 or 56,064 products in another order)
+        assert torch.allclose(got, want, rtol=1e-4, atol=1e-4), (got, want)
+        one.close()
+    group.close()

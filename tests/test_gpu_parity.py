@@ -323,6 +323,23 @@ def test_cnn_fp32_split_shapes(conv, pool, hw, fy):
     _cnn_case(spec, n_frames=16, n_img=1, fy=fy, max_count=600)
 
 
+@pytest.mark.parametrize("conv,pool,hw,bf16", [
+    ((16,), (True,), (4, 1200), False),
+    ((48, 16), (False, True), (5, 1135), False),
+    ((64,), (True,), (6, 1201), False),
+    ((16,), (True,), (4, 3500), True),
+    ((32,), (False,), (2, 3412), True),
+    ((96,), (True,), (5, 3413), True),
+])
+def test_cnn_first_layer_of_wide_maps(conv, pool, hw, bf16):
+    """First layers of which one tile row exceeds the LDS of the kernels for
+    usual widths: column segments."""
+    spec = synth.CNNSpec(in_h=hw[0], in_w=hw[1], conv=conv, pool=pool, dense=16, bf16=bf16)
+    _cnn_case(spec, n_frames=5, n_img=3)
+    if bf16:
+        _cnn_case(spec, n_frames=5, n_img=2, pairs=True)
+
+
 @pytest.mark.parametrize("conv,pool,hw,fy", [
     ((64, 64), (True, True), (50, 50), 2),    # pooled 64 channels, nested cells: fp16 into a band
     ((16,), (True,), (7, 5), 1),              # one store lane of four, a last pooled row cut off
@@ -860,16 +877,52 @@ def test_skipping_streamed_equals_one_shot():
     print(check_samples(wl, v, blob, lr, None, g, [0, 1, 2, 301, 302, 603, 1299]))
 
 
+@pytest.mark.parametrize("H,W", [
+    (11, 31),   # 1,023 values: one wave per frame, the last one that does (4-byte loads)
+    (17, 20),   # 1,020: one wave, 16-byte loads
+    (18, 19),   # 1,026: four waves, 4-byte loads
+    (12, 29),   # 1,044: four waves, 16-byte loads, the last wave's batch nearly empty
+    (37, 37),   # 4,107: frames at every alignment
+])
+@pytest.mark.parametrize("metric", [W.MSE, W.SAD, W.NRMSE])
+def test_detector_global_forms(H, W, metric):
+    """The global score by one wave per frame and by four, on both sides of
+    the 1,024 values where the form changes, against the oracle."""
+    n, delta = 37, 2
+    f = rng.integers(0, 256, size=(n, H, W, 3), dtype=np.uint8)
+    f[5:9] = f[3]
+    f[20] = f[18] = 0
+    cfg = nsc.make_cfg(in_h=H, in_w=W, dd_h=H, dd_w=W, cnn_h=H, cnn_w=W, delta=delta,
+                       delta_diff=0.0, metric=metric)
+    sums = torch.empty((n, H, W, 3), dtype=torch.int32, device=DEV)
+    fire = torch.empty(n, dtype=torch.uint8, device=DEV)
+    score = torch.empty(n, dtype=torch.float64, device=DEV)
+    nsc.nsc_diff_detect(cfg, _dev(f), n, 0, sums, fire, score_out=score)
+    S, g = f.astype(np.int32), score.cpu().numpy()
+    assert np.array_equal(sums.cpu().numpy(), S) and np.isinf(g[:delta]).all()
+    for i in range(delta, n):
+        exp = oracle.global_metric(S[i], S[i - delta], 1, metric)[0]
+        assert g[i] == exp, (i, g[i], exp)
+    assert np.array_equal(fire.cpu().numpy(), (g > 0).astype(np.uint8))
+
+
 @pytest.mark.parametrize("H,W,grid", [
-    (12, 10, (3, 5)),      # rows of blocks, one slot per lane
+    # blocked frames of more than 1,024 values: one wave per frame in the whole
+    # call (from 16,384 frames on), four in the part
+    (30, 40, (3, 5)),      # rows of blocks, two slots per lane
+    (18, 21, (18, 21)),    # one slot per lane, blocks of one cell, more rows of blocks than waves
+    (20, 100, (2, 7)),     # five slots per lane, fewer rows of blocks than waves
     (20, 130, (7, 13)),    # rows of 390 values: the general block walk
     (8, 72, (2, 70)),      # more block columns than lanes
+    # one wave per frame in both
+    (12, 10, (3, 5)),
     (6, 8, (1, 1)),
+    # four in both (the global score's form does not depend on the call)
+    (18, 20, (1, 1)),
 ])
 def test_detector_frame_splits(H, W, grid):
-    """A call scored by one wave per frame (blocked, from 16,384 frames on) or
-    four gives the scores of the same frames in small calls, bit for bit, and
-    the oracle's at sampled frames."""
+    """A call of 16,400 frames gives the scores of the same frames in a call of
+    300, bit for bit, and the oracle's at sampled frames."""
     n, delta = 16_400, 3
     frames = torch.from_numpy(rng.integers(0, 256, size=(n, H, W, 3), dtype=np.uint8)).to(DEV)
     lr = rng.standard_normal(grid[0] * grid[1]).astype(np.float32)
