@@ -76,13 +76,24 @@ def area_kernel(wl) -> str:
     """The area kernel a workload's cascade runs: with fuse_prev set, against
     an earlier frame at least two frames back with the global MSE metric and
     16-byte lane chunks, the one with the detector fused in
-    (k_area_prev_wave); otherwise k_area_sums_wave (which fuses the global
+    (k_area_prev_wave); for 256 or more frames a call that fit LDS whole with
+    their grid's tables and whose cells touch at most 4 pixels,
+    k_area_sums_small; otherwise k_area_sums_wave (which fuses the global
     detector against a fixed reference image)."""
     delta = wl.delta // max(1, getattr(wl, "check_stride", 1))  # in checked frames
     if getattr(wl, "fuse_prev", 0) and wl.ref_mode == 0 and delta >= 2 and \
             getattr(wl, "metric", 0) == 0 and tuple(wl.grid) == (1, 1) and \
             lane_chunk_bytes(wl.video.w, wl.dd_w) == 16:
         return "k_area_prev_wave"
+
+    def touched(n_in, n_out):  # pixels of an axis that an output cell touches at most
+        g = math.gcd(n_in, n_out)
+        p, q = n_in // g, n_out // g
+        return p if q == 1 else (p - 1) // q + 2
+    h, w = wl.video.h, wl.video.w
+    if 3 * h * w + 16 * (wl.dd_h + wl.dd_w) <= 52 * 1024 and wl.video.n >= 256 and \
+            touched(h, wl.dd_h) * touched(w, wl.dd_w) <= 4:
+        return "k_area_sums_small"
     return AREA_KERNEL
 
 
@@ -169,7 +180,7 @@ def measured_traffic(workload: str, kernel: str = AREA_KERNEL):
 
 
 CNN_SOURCES = ("paper_1703_02529_amd/csrc/cnn.hip", "paper_1703_02529_amd/csrc/nsc_internal.h")
-CNN_KERNELS = "k_conv,k_prep_input,k_pair64,k_band64,k_dense"
+CNN_KERNELS = "k_conv,k_first,k_prep_input,k_pair64,k_band64,k_dense"
 
 
 def measured_mfma_busy(workload: str):

@@ -57,6 +57,7 @@ def test_area_kernel_names_match_the_library_plan():
     assert bench.lane_chunk_bytes(1920, 100) == 16   # 54 of 64
     assert bench.lane_chunk_bytes(1280, 50) == 32    # 48 of 64 at 16 bytes, 60 at 32
     for wl in W.ALL:
-        assert bench.area_kernel(wl) == "k_area_sums_wave", wl.name
+        small = wl is W.TINY  # 30,000-byte frames, cells of 2x2 pixels
+        assert bench.area_kernel(wl) == ("k_area_sums_small" if small else "k_area_sums_wave"), wl.name
     fused = types.SimpleNamespace(**vars(W.VGA), fuse_prev=1)  # a description asking for it
     assert bench.area_kernel(fused) == "k_area_prev_wave"
