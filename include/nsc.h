@@ -75,7 +75,13 @@ enum { NSC_REF_PREV = 0, NSC_REF_FIXED = 1 };
  * sums; PSNR goes through the device log10 (within a few ulp). */
 enum { NSC_METRIC_MSE = 0, NSC_METRIC_SAD = 1, NSC_METRIC_NRMSE = 2, NSC_METRIC_PSNR = 3 };
 /* Element types of a specialized CNN (its weights and activations):
- *   NSC_F32        fp32 weights and activations, fp32 matrix cores;
+ *   NSC_F32        fp32 weights and activations, fp32 accumulation.  The first
+ *                  layer and the inner layers whose input channels are a
+ *                  multiple of 32 form their products on the bf16 matrix cores,
+ *                  each operand as the exact sum of three bf16 values and six
+ *                  of the nine partial products: at most 2^-24 of a product is
+ *                  left out, of either sign (maps too wide for these kernels,
+ *                  other inner layers and the dense layer: fp32 matrix cores);
  *   NSC_BF16       bf16 weights; the pre-processed input rounded to bf16; the
  *                  64-input-channel layers and the dense layer run on the fp16
  *                  matrix cores with their activations rounded to fp16 (the

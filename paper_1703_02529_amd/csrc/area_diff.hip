@@ -1088,8 +1088,9 @@ int make_area_plan(int32_t in_h, int32_t in_w, int64_t stride, const void* frame
       // faster, 1280x720 -> 100x100 0 and 6 %, 1920x1080 -> 100x100 1.2 and
       // 1 %, 1280x720 -> 50x50 within 0.5 %; a single row was faster still at
       // 640x480 but 5 % slower at 1280x720 -> 100x100.  Rows of a few hundred
-      // bytes (4-byte chunks) keep bands of about 10 rows: 100x100 -> 50x50,
-      // 20,000 frames, 663 us against 847 with two rows.
+      // bytes (4-byte chunks; calls of few output rows and the fused detectors)
+      // keep bands of about 10 rows: 100x100 -> 50x50, 20,000 frames, 663 us
+      // against 847 with two rows.
       int64_t wb = best_cb >= 16 ? (out_h + 1) / 2 : (out_h + 9) / 10;
       const int64_t fill = (16384 + n * g.waves_per_frame - 1) / (n * g.waves_per_frame > 0 ? n * g.waves_per_frame : 1);
       if (fill > wb) wb = fill;

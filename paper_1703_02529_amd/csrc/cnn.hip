@@ -9,8 +9,10 @@
 // input band (4 output rows + halo, zero padded) in LDS per item.  The first
 // layer's staging gathers the survivor's area sums, sums nested cells and
 // applies the [-1, 1] pre-processing.  bf16 layers use
-// v_mfma_f32_16x16x32_bf16, fp32 layers v_mfma_f32_16x16x4_f32; both
-// accumulate in fp32.
+// v_mfma_f32_16x16x32_bf16; so do the first and the 32 k-input-channel layers
+// of fp32 networks, their operands as three bf16 parts each, while their other
+// conv layers and their dense layer use v_mfma_f32_16x16x4_f32.  All accumulate
+// in fp32.
 //
 // A bf16 network has bf16 weights and a bf16-rounded input.  Its later
 // activations enter the matrix cores in one of two ways:
@@ -1005,10 +1007,11 @@ __device__ __forceinline__ void band64_clear(unsigned char* lds, const Band64& b
     *reinterpret_cast<uint4*>(lds + (size_t)i * 16) = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// floor(pix / w) for a band pixel index, without an integer division.  A
-// band's pixels fit the LDS (pix < rows * wb <= 1280), so the exact quotient
-// (pix + 1/2) / w lies at least 1 / (2 w) >= 3.9e-4 from an integer, while the
-// two fp32 roundings move it by at most 2^-23 of itself (< 1.6e-4).
+// floor(pix / w) for a band pixel index, without an integer division.  The
+// exact quotient (pix + 1/2) / w lies at least 1 / (2 w) from an integer, while
+// the two fp32 roundings (of 1 / w and of the product; pix + 1/2 is exact) move
+// it by at most 2^-23 (pix + 1/2) / w: right for every pix below 2^22 - 1, and
+// a band's pixels fit the LDS (at most about 20,000, of 8 bytes).
 __device__ __forceinline__ int band_row(int pix, float inv_w) {
   return (int)(((float)pix + 0.5f) * inv_w);
 }
@@ -3277,8 +3280,7 @@ bool x3_plan(const CnnLayer& L, int32_t max_bt, Band64* b, int32_t* band_tiles, 
       bt = c;
     }
   }
-  // band_row's exactness bound on the pixels of a band
-  if (band64_bytes(plan(bt)) > 160 * 1024 || plan(bt).rows * wb > 1280) return false;
+  if (band64_bytes(plan(bt)) > 160 * 1024) return false;
   *b = plan(bt);
   *band_tiles = bt;
   *lds = band64_bytes(*b);
@@ -3515,8 +3517,8 @@ int run_cnn(const Cnn& cnn, const CnnRunArgs& r, void* ws, size_t ws_bytes, hipS
     }
     for (int l = 0; l < cnn.n_layers; ++l)
       out16[l] = band[l] && (l + 1 < cnn.n_layers ? band[l + 1] : cnn.h16);
-    // a first layer run alone (k_conv_first) writes fp16 for a banded fp16
-    // second layer
+    // a first layer run alone (k_first_bf16, or k_conv_first on the widest maps)
+    // writes fp16 for a banded fp16 second layer
     if (!p64 && !pair && cnn.n_layers > 1) out16[0] = band[1];
   }
   auto set_formats = [&](ConvArgs& a, int l) {
