@@ -705,7 +705,11 @@ __global__ void __launch_bounds__(256) k_area_prev_wave(const uint8_t* __restric
 // 67.6 (2,040), 392 against 417 (16,384, delta 1).  At 32,768 blocked frames
 // (delta 30) one wave per frame took 854 us, four 1,022 and the dealt order
 // 864: the sums no longer stay in the last-level cache between the two reads,
-// and fewer frames in flight keep more of them there.
+// and fewer frames in flight keep more of them there.  Blocked scores of small
+// grids are four waves' work only in small calls (4x4 blocks, delta 15: 18x20
+// sums, 2,000 frames 8.5 us against 9.2, 8,000 frames 24.9 against 20.8; 24x24,
+// 8,000 frames 28.4 against 23.7; 32x32, 4,000 frames 18.2 against 18.0; 40x40,
+// 8,000 frames 38 against 46).
 constexpr int64_t kDiffWideBlocked = 16384;
 
 // Blocked score by rows: a wave streams block rows (of its share) row by row,
@@ -743,6 +747,8 @@ __device__ __forceinline__ double block_row_terms(const int32_t* __restrict__ cu
   for (int by = wave; by < grid_h; by += W) {
     const int y0 = (int)((int64_t)by * a.dd_h / grid_h);
     const int y1 = (int)((int64_t)(by + 1) * a.dd_h / grid_h);
+    // loaded here, in flight with the row loads
+    const float weight = lane < grid_w ? lr_w[by * grid_w + lane] : 0.0f;
     DiffSums<M> acc[J];
 #pragma unroll 2
     for (int y = y0; y < y1; ++y) {
@@ -781,7 +787,7 @@ __device__ __forceinline__ double block_row_terms(const int32_t* __restrict__ cu
       const int x0 = (int)((int64_t)lane * a.dd_w / grid_w);
       const int x1 = (int)((int64_t)(lane + 1) * a.dd_w / grid_w);
       const double ncell = ((double)(y1 - y0) * (double)(x1 - x0)) * 3.0;
-      term = (double)lr_w[by * grid_w + lane] * b.value(a, ncell);
+      term = (double)weight * b.value(a, ncell);
       if constexpr (W > 1) terms[by * grid_w + lane] = term;
     }
     __syncwarp();  // sums read before the next block row clears them
@@ -1255,7 +1261,9 @@ int launch_diff(const DiffArgs& a, hipStream_t stream) {
   const bool blocked = a.cams ? a.cams_blocked != 0 : a.grid_h * a.grid_w > 1;
   // four waves per frame; one where a frame is no more than a load or two of a wave
   // (65,536 frames of 8x8 sums: 20 us against 60)
-  const bool wide = (int64_t)a.dd_h * a.dd_w * 3 > 1024 && (!blocked || a.n < kDiffWideBlocked);
+  const int64_t values = (int64_t)a.dd_h * a.dd_w * 3;
+  const bool wide =
+      values > 1024 && (!blocked || a.n < (values < kDiffWideBlocked / 2 ? 2 * values : kDiffWideBlocked));
   const int64_t blocks = wide ? a.n : (a.n + 3) / 4;
   if (blocks > 0x7FFFFFFF) return fail(NSC_E_SHAPE, "too many frames in one call");
 #define NSC_DIFF_LAUNCH2(K, M)                                                                \

@@ -906,6 +906,30 @@ def test_detector_global_forms(H, W, metric):
     assert np.array_equal(fire.cpu().numpy(), (g > 0).astype(np.uint8))
 
 
+@pytest.mark.parametrize("H,W,grid", [(18, 21, (18, 21)), (18, 19, (1, 5)), (9, 70, (4, 66))])
+def test_detector_blocked_forms_by_call_size(H, W, grid):
+    """Blocked scores of small grids in the last call size with four waves per
+    frame (2 x 3 H W - 1 frames) and the first with one: the same bits, and the
+    oracle's."""
+    n, delta = 6 * H * W, 4
+    frames = torch.from_numpy(rng.integers(0, 256, size=(n, H, W, 3), dtype=np.uint8)).to(DEV)
+    lr = rng.standard_normal(grid[0] * grid[1]).astype(np.float32)
+    lr_dev = _dev(lr)
+    cfg = nsc.make_cfg(in_h=H, in_w=W, dd_h=H, dd_w=W, cnn_h=H, cnn_w=W, delta=delta, grid=grid,
+                       lr_w=lr_dev, lr_b=-0.5, delta_diff=0.0, metric=1)
+    got = []
+    for m in (n - 1, n):
+        sums = torch.empty((m, H, W, 3), dtype=torch.int32, device=DEV)
+        fire = torch.empty(m, dtype=torch.uint8, device=DEV)
+        score = torch.empty(m, dtype=torch.float64, device=DEV)
+        nsc.nsc_diff_detect(cfg, frames, m, 0, sums, fire, score_out=score)
+        got.append(score.cpu().numpy())
+    assert np.array_equal(got[0], got[1][:-1])
+    S = frames.cpu().numpy().astype(np.int32)
+    for i in (delta, n // 2, n - 1):
+        assert got[1][i] == oracle.blocked_metric(S[i], S[i - delta], 1, grid, lr, -0.5, 1)[0]
+
+
 @pytest.mark.parametrize("H,W,grid", [
     # blocked frames of more than 1,024 values: one wave per frame in the whole
     # call (from 16,384 frames on), four in the part
