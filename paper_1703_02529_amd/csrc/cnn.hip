@@ -121,9 +121,10 @@ __device__ __forceinline__ uint16_t div_to_bf16_bits_fast(int32_t N, int32_t D, 
 
 // A value whose origin the compiler does not see.  Two 8-byte LDS reads 8 bytes
 // apart at an 8-byte-aligned address are merged into one 16-byte read, which
-// stalls the LDS for about 45 cycles where it is not 16-byte aligned
-// (SQ_LDS_UNALIGNED_STALL); with the distance of the second read opaque they
-// stay two reads of a few cycles each.
+// stalls the LDS for about 36 cycles where it is not 16-byte aligned; with the
+// distance of the second read opaque they stay two reads of a few cycles each.
+// (k_first_x3, 3,000 images: 276 us and 84.8 M SQ_LDS_UNALIGNED_STALL cycles
+// for 2.4 M merged reads, against 173 us and none.)
 __device__ __forceinline__ int opaque(int v) {
   asm("" : "+v"(v));
   return v;
@@ -1765,10 +1766,10 @@ __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& 
 // per plane): 32 input channels at a time go into three LDS planes, the
 // weights of a tap come from L2 one step ahead, and a wave keeps up to
 // x3_tiles tiles of 16 pixels x 16 NT output channels.  Bound by the matrix
-// cores (6 x 9 x cin / 32 MFMAs per tile and 16 channels: 42 % busy) and the
-// stream of weights from L2.  3,000 images, 32 -> 32 channels, 25x25: 206 us
+// cores (6 x 9 x cin / 32 MFMAs per tile and 16 channels: 40 % busy) and the
+// stream of weights from L2.  3,000 images, 32 -> 32 channels, 25x25: 211 us
 // against 570 on the fp32 cores; 1,000 images of the 64-channel 4-layer
-// network 1.90 ms against 27.4, whose weights left room for one tile row in
+// network 1.89 ms against 27.4, whose weights left room for one tile row in
 // the LDS.
 constexpr int x3_tiles(int nt) { return nt <= 2 ? 4 : 3; }
 
@@ -1994,9 +1995,10 @@ k_conv_x3(ConvArgs a, Band64 b) {
 // h m' | m h' and h l' | l h', and m m'), so a tile takes 10 MFMAs per 16
 // channels.  Pixels run along the band in raster order
 // (4 pooling windows per tile on a pooling layer), the lane's position
-// carried from tile to tile.  Bound by instruction issue (45 vector
-// instructions and 20 MFMAs per tile) and the input gather's latency.  3,000
-// images of 50x50, 32 channels: 150 us against 335 on the fp32 cores.
+// carried from tile to tile.  Bound by instruction issue (98
+// vector instructions per tile, the staging's among them, 20 of them MFMAs:
+// matrix cores 42 % busy) and the input gather's latency.  3,000 images of
+// 50x50, 32 channels: 160 us against 335 on the fp32 cores.
 struct FirstX3 {
   int32_t bw;          // staged pixels per band row (image columns -1 .. bw - 2)
   double inv255;       // 1 / (255 den)
@@ -2196,7 +2198,7 @@ __global__ void __launch_bounds__(256)
 // layers, so that it rounds as theirs do.  Stores fp32, or fp16 times the next
 // layer's input scale.  Bound
 // by the gather of the area sums and its latency.  1,501 images of 100x100
-// sums, 64 channels: 104 us against 125 with the weights in LDS and a
+// sums, 64 channels: 111 us against 125 with the weights in LDS and a
 // 2-byte store per value (k_conv_first).
 template <int NT, bool POOL, bool G>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
