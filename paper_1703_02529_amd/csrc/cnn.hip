@@ -1989,16 +1989,16 @@ k_conv_x3(ConvArgs a, Band64 b) {
 
 // First layer of an fp32 network (3 input channels): the survivor's area sums
 // become fp32 inputs, each pixel 24 bytes of LDS: the h, m and l parts of its
-// 4 channels (the fourth 0), read 8 bytes at a time (see opaque()).  K is (dy, dx of 4, c of 4) = 48 of 64: a first MFMA step takes dy 0
-// and 1, and the half-used second one (dy 2) carries a second partial product
-// in its upper half (h h' alone, whose accumulator then holds it exactly, pairs
-// h m' | m h' and h l' | l h', and m m'), so a tile takes 10 MFMAs per 16
-// channels.  Pixels run along the band in raster order
-// (4 pooling windows per tile on a pooling layer), the lane's position
-// carried from tile to tile.  Bound by instruction issue (98
-// vector instructions per tile, the staging's among them, 20 of them MFMAs:
-// matrix cores 42 % busy) and the input gather's latency.  3,000 images of
-// 50x50, 32 channels: 160 us against 335 on the fp32 cores.
+// 4 channels (the fourth 0), read 8 bytes at a time (see opaque()).  K is (dy,
+// dx of 4, c of 4) = 48 of 64: a first MFMA step takes dy 0 and 1, and the
+// half-used second one (dy 2) carries a second partial product in its upper
+// half (h h' alone, whose accumulator then holds it exactly, pairs h m' | m h'
+// and h l' | l h', and m m'), so a tile takes 10 MFMAs per 16 channels.  Pixels
+// run along the band in raster order (4 pooling windows per tile on a pooling
+// layer), the lane's position carried from tile to tile.  Bound by instruction
+// issue (98 vector instructions per tile, the staging's among them, 20 of them
+// MFMAs: matrix cores 42 % busy) and the input gather's latency.  3,000 images
+// of 50x50, 32 channels: 160 us against 335 on the fp32 cores.
 struct FirstX3 {
   int32_t bw;          // staged pixels per band row (image columns -1 .. bw - 2)
   double inv255;       // 1 / (255 den)
