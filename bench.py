@@ -122,7 +122,8 @@ BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 DTYPE_BF16 = ("u8 frames, i32/i64 detector; CNN: bf16 weights and input; fp16 activations on "
               "the fp16 matrix cores in the 64-channel and dense layers, bf16 hi/lo activation "
               "pairs in the others; fp32 accumulate")
-DTYPE_FP32 = "u8 frames, i32/i64 detector; CNN: fp32 weights and activations, fp32 MFMA"
+DTYPE_FP32 = ("u8 frames, i32/i64 detector; CNN: fp32 weights and activations, conv products from three "
+              "bf16 parts of each operand (at most 2^-24 left out), fp32 accumulate")
 FP32_PEAK_TFLOPS = 157.3
 
 
